@@ -837,24 +837,40 @@ __global__ void zero_tiles_kernel(const TileDesc* __restrict__ tiles, int S) {
 }
 
 // probe_grad[y][x] (+)= sum over the workgroups' partial sums, which hold pixel
-// (y, x) = (Y2*r + n2, x) at index r*T + n2*M + x (layout A).  The sum runs in
-// workgroup order, so the result does not depend on timing.
+// (y, x) = (Y2*r + n2, x) at index r*T + n2*M + x (layout A).  Bound by reading
+// the partials (33.5 MB for 256 of 128 x 128) at the latency of as many loads
+// as are in flight: a workgroup takes 64 consecutive pixels and its 16 waves
+// every 16th partial, four loads at a time; the waves' sums are added in wave
+// order, so the result does not depend on timing.  One thread per pixel walking
+// all partials in turn took 62 us for 256 of them, this 10 us.
+constexpr int kReduceWaves = 16;
 template <int M>
-__global__ void probe_reduce_kernel(const float2* __restrict__ part, int parts, float2* __restrict__ out,
-                                    int accumulate) {
+__global__ void __launch_bounds__(64 * kReduceWaves) probe_reduce_kernel(const float2* __restrict__ part, int parts,
+                                                                         float2* __restrict__ out, int accumulate) {
   using G = Geo<M>;
-  const int i = static_cast<int>(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= M * M) return;
+  __shared__ float2 sums[kReduceWaves][64];
+  const int lane = static_cast<int>(threadIdx.x & 63), wave = static_cast<int>(threadIdx.x >> 6);
+  const int i = static_cast<int>(blockIdx.x) * 64 + lane;  // < M*M: the grid is exact
+  const float2* __restrict__ p = part + i;
+  float2 s = make_float2(0.f, 0.f);
+  int b = wave;
+  for (; b + 3 * kReduceWaves < parts; b += 4 * kReduceWaves) {
+    float2 v[4];
+    sfor<4>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
+      v[k] = p[static_cast<long long>(b + k * kReduceWaves) * (M * M)];
+    });
+    s = cadd(s, cadd(cadd(v[0], v[1]), cadd(v[2], v[3])));
+  }
+  for (; b < parts; b += kReduceWaves) s = cadd(s, p[static_cast<long long>(b) * (M * M)]);
+  sums[wave][lane] = s;
+  __syncthreads();
+  if (wave != 0) return;
+  for (int w = 1; w < kReduceWaves; ++w) s = cadd(s, sums[w][lane]);
   const int r = i / G::T, tid = i % G::T;
   const int y = G::Y2 * r + tid / M, x = tid % M;
-  float sx = 0.f, sy = 0.f;
-  for (int b = 0; b < parts; ++b) {
-    const float2 v = part[static_cast<long long>(b) * (M * M) + i];
-    sx += v.x;
-    sy += v.y;
-  }
   float2& o = out[y * M + x];
-  o = accumulate ? make_float2(o.x + sx, o.y + sy) : make_float2(sx, sy);
+  o = accumulate ? cadd(o, s) : s;
 }
 
 // ---------------------------------------------------------------------------
@@ -1025,12 +1041,12 @@ hipError_t launch_zero_tiles(const TileDesc* tiles, int ntiles, int S, hipStream
 
 hipError_t launch_probe_reduce(const float2* part, int parts, int M, float2* probe_grad, bool accumulate,
                                hipStream_t st) {
-  const unsigned blocks = static_cast<unsigned>((M * M + 255) / 256);
+  const unsigned blocks = static_cast<unsigned>(M * M / 64);
   if (M == 128) {
-    hipLaunchKernelGGL(probe_reduce_kernel<128>, dim3(blocks), dim3(256), 0, st, part, parts, probe_grad,
+    hipLaunchKernelGGL(probe_reduce_kernel<128>, dim3(blocks), dim3(64 * kReduceWaves), 0, st, part, parts, probe_grad,
                        accumulate ? 1 : 0);
   } else if (M == 64) {
-    hipLaunchKernelGGL(probe_reduce_kernel<64>, dim3(blocks), dim3(256), 0, st, part, parts, probe_grad,
+    hipLaunchKernelGGL(probe_reduce_kernel<64>, dim3(blocks), dim3(64 * kReduceWaves), 0, st, part, parts, probe_grad,
                        accumulate ? 1 : 0);
   } else {
     return hipErrorInvalidValue;
