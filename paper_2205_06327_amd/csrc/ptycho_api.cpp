@@ -243,7 +243,12 @@ int ptycho_create(ptycho_ctx** out, int32_t M, int32_t S, double wavelength_A, d
     free_ctx(c);
     return hip_fail(e, "device query");
   }
-  c->grid = cus > 0 ? cus : 256;  // one workgroup per CU (LDS-bound occupancy)
+  // Persistent workgroups: as many as the device holds at once (fused_workgroups_per_cu).  One 64-window
+  // workgroup per CU left each SIMD a single wave and nothing to issue while it waited: 1107 two-slice
+  // positions (a pass with its shifted probes) took 170 us with 256 workgroups and 144 us with 768, 1640
+  // eight-slice patterns 235 and 111 us.
+  const int per_cu = ptycho::fused_workgroups_per_cu(M);
+  c->grid = (cus > 0 ? cus : 256) * per_cu;
   c->capacity = max_positions > 0 ? max_positions : 4096;
 
   // Tables computed in double precision, rounded once to float.
@@ -255,12 +260,19 @@ int ptycho_create(ptycho_ctx** out, int32_t M, int32_t S, double wavelength_A, d
     const double ph = -kPi * wavelength_A * dz_A * f * f;
     h[e2] = make_float2(static_cast<float>(std::cos(ph)), static_cast<float>(std::sin(ph)));
   }
-  const size_t ws_elems = static_cast<size_t>(c->grid) * ptycho::ws_slots(S, 1) * M * M;
+  size_t ws_elems = static_cast<size_t>(c->grid) * ptycho::ws_slots(S, 1) * M * M;
+  if (per_cu > 1 && ws_elems > 0 && hipMalloc(&c->d_ws, ws_elems * sizeof(float2)) != hipSuccess) {
+    // no room for the larger store: one workgroup per CU
+    (void)hipGetLastError();
+    c->d_ws = nullptr;
+    c->grid /= per_cu;
+    ws_elems /= per_cu;
+  }
   if ((e = hipMalloc(&c->d_tw, M * sizeof(float2))) != hipSuccess ||
       (e = hipMalloc(&c->d_h, M * sizeof(float2))) != hipSuccess ||
       (e = hipMalloc(&c->d_loss, static_cast<size_t>(c->capacity) * sizeof(double))) != hipSuccess ||
       (e = hipMalloc(&c->d_status, sizeof(unsigned))) != hipSuccess ||
-      (ws_elems > 0 && (e = hipMalloc(&c->d_ws, ws_elems * sizeof(float2))) != hipSuccess) ||
+      (ws_elems > 0 && !c->d_ws && (e = hipMalloc(&c->d_ws, ws_elems * sizeof(float2))) != hipSuccess) ||
       (e = hipMalloc(&c->d_probe_part, static_cast<size_t>(c->grid) * M * M * sizeof(float2))) != hipSuccess ||
       (e = hipMalloc(&c->d_tiles, ptycho::kMaxTiles * sizeof(ptycho::TileDesc))) != hipSuccess) {
     free_ctx(c);

@@ -532,11 +532,10 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
   return f;
 }
 
-// Waves per SIMD the position kernels are compiled for: a 128-window workgroup
-// (8 waves, 136 KB of LDS) fills a CU alone; three 64-window workgroups (4
-// waves, 35 KB of LDS each) share one, which caps the registers at 168 per lane.
+// Waves per SIMD the position kernels are compiled for: the workgroups that
+// share a CU times their waves, over 4 SIMDs.
 template <int M>
-constexpr int kWavesPerSimd = M == 64 ? 3 : 2;
+constexpr int kWavesPerSimd = fused_workgroups_per_cu(M) * Geo<M>::T / 256;
 
 template <int M, int MODE>
 __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(KernelArgs a) {

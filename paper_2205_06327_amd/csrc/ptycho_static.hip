@@ -82,7 +82,8 @@ int static_device(StaticDevice* out) {
 }
 
 // Checkpoint interval and workgroup count for which the incident-wave store fits the array: the most
-// workgroups (up to one per CU), then the shortest interval (the least recomputation).
+// workgroups up to one per CU, then the shortest interval (the least recomputation), then, at that
+// interval, as many workgroups as fit and share the CUs.
 void fit_wave_store(int M, int S, int cus, int* ck_out, int* grid_out) {
   const size_t slot = size_t(M) * M * sizeof(float2);
   const size_t slots = kWaveBytes / slot;
@@ -97,7 +98,10 @@ void fit_wave_store(int M, int S, int cus, int* ck_out, int* grid_out) {
     }
   }
   *ck_out = best_ck;
-  *grid_out = best_grid;
+  const int per = ptycho::ws_slots(S, best_ck);
+  const size_t most = size_t(cus) * ptycho::fused_workgroups_per_cu(M);
+  const size_t g = per == 0 ? most : slots / per;
+  *grid_out = best_grid < cus ? best_grid : static_cast<int>(g < most ? g : most);
 }
 
 }  // namespace
