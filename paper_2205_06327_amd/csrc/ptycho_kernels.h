@@ -36,6 +36,7 @@ constexpr int kMaxTiles = 4096;
 
 struct KernelArgs {
   int M, S, n;
+  int run;               // consecutive positions per workgroup (set by launch_fused)
   // object window source: element (s, y, x) at obj[s*slice_stride + y*ld + x], y, x local to the box
   const float2* obj;
   long long slice_stride, ld;

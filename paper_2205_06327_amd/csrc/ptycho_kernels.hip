@@ -13,8 +13,8 @@
 // workspace in HBM (all of them, or checkpoints from which the adjoint sweep
 // recomputes the rest) and re-read in reverse order by the adjoint sweep.
 // Gradient windows are added to the caller's gradient with hardware float
-// atomics, each instruction covering whole 128-byte lines (128-windows) or 32
-// contiguous complex values (64-windows and the batched launch).  Optional
+// atomics; the windows are held rolled to the gradient's 128-byte lines, so
+// each instruction covers two whole lines.  Optional
 // outputs: the probe gradient (per-workgroup partial sums).
 #include "fft_lds.hpp"
 #include "ptycho_kernels.h"
@@ -60,19 +60,30 @@ __device__ __forceinline__ void load_slot(float2 (&v)[R], const float2* slot, in
 // Position index of the j-th job of this workgroup, or -1 when done.  Blocks
 // are dispatched round-robin over the 8 XCDs; the positions are cut into 8
 // contiguous chunks and chunk x is walked by the blocks of XCD x, so blocks
-// sharing an L2 work on neighbouring (overlapping) windows.
-__device__ __forceinline__ int job_position(int j, int n, int grid) {
+// sharing an L2 work on neighbouring (overlapping) windows.  Each block takes
+// runs of `run` consecutive positions, so that the windows in flight lie `run`
+// scan steps apart: with single positions all blocks of an XCD add to almost
+// the same gradient lines at the same time, and the memory side's atomics
+// queue (launch_run has the figures).  The remainder of a chunk that no longer
+// fills a round of runs is split evenly, so no block gets more than
+// ceil(chunk / blocks) positions; the blocks with one more are the first ones,
+// which sit on different CUs (spread over the chunk they shared CUs: 1640
+// eight-slice patterns of 64-windows took 135 us instead of 109).
+__device__ __forceinline__ int job_position(int j, int n, int grid, int run) {
   const int b = static_cast<int>(blockIdx.x);
   if (grid < 8) {
     int p = b + j * grid;
     return p < n ? p : -1;
   }
-  const int x = b & 7;
+  const int x = b & 7, k = b >> 3;
   const int gx = (grid - x + 7) >> 3;              // blocks on this XCD
   const int lo = static_cast<int>((static_cast<long long>(x) * n) >> 3);
   const int hi = static_cast<int>((static_cast<long long>(x + 1) * n) >> 3);
-  int p = lo + (b >> 3) + j * gx;
-  return p < hi ? p : -1;
+  const int rounds = (hi - lo) / (gx * run);       // whole rounds of runs
+  if (j < rounds * run) return lo + ((j / run) * gx + k) * run + j % run;
+  const int r0 = lo + rounds * gx * run, rem = hi - r0;  // rem < gx * run
+  const int base = rem / gx, more = rem % gx, i = j - rounds * run;
+  return i < base + (k < more ? 1 : 0) ? r0 + k * base + (k < more ? k : more) + i : -1;
 }
 
 template <class G>
@@ -171,43 +182,62 @@ __device__ __forceinline__ void idft2_c_to_a(float2 (&v)[G::R], float2* lds, con
   pass_a_inv<G>(v, L.n2);
 }
 
-// Window of the current position in layout A: row y = Y2*r + n2, column x.
+// Windows are held rolled along x: lane x of layout A holds window column
+// (x - roll) mod M, `col` below.  A cyclic shift of the wave multiplies its DFT
+// by a unit-modulus ramp along kx, so it commutes with the propagator and
+// leaves |Psi| and the real factor that the residual puts on Psi unchanged:
+// the sweeps need nothing but the same roll in every load and store.  The roll
+// is the window's offset from a 128-byte line (window_roll), so that lanes
+// x = 16k .. 16k+15 access whole lines of the object and of the gradient
+// wherever the window starts.
+__device__ __forceinline__ int window_roll(const float2* origin, long long ld, long long sstride, int S) {
+  const bool same = (ld & 15) == 0 && (S == 1 || (sstride & 15) == 0);  // one offset for all rows
+  return same ? static_cast<int>((reinterpret_cast<unsigned long long>(origin) >> 3) & 15) : 0;
+}
+template <class G>
+__device__ __forceinline__ int window_col(int x, int roll) {
+  return (x - roll) & (G::M - 1);
+}
+// Window of the current position in layout A: row y = Y2*r + n2, column col.
 // `base` is uniform across the workgroup; each row pointer is computed on the
 // scalar unit and the lane offset is the column, so the loads use the
 // scalar-base + 32-bit lane-offset addressing form.
 template <class G, class F>
-__device__ __forceinline__ void for_window_rows(const float2* __restrict__ base, long long ld, const Lanes<G>& L,
-                                                F&& f) {
+__device__ __forceinline__ void for_window_rows(const float2* __restrict__ base, long long ld, int col,
+                                                const Lanes<G>& L, F&& f) {
   const int ldz = static_cast<int>(ld) + opaque_zero();
   base += static_cast<long long>(L.n2) * ldz;
   sfor<G::R>([&](auto rc) {
     constexpr int r = decltype(rc)::value;
     const float2* __restrict__ row = base + static_cast<long long>(r * G::Y2 * ldz);
-    f(rc, row[L.x]);
+    f(rc, row[col]);
   });
 }
 template <class G>
-__device__ __forceinline__ void load_window(float2 (&t)[G::R], const float2* __restrict__ base, long long ld,
+__device__ __forceinline__ void load_window(float2 (&t)[G::R], const float2* __restrict__ base, long long ld, int col,
                                             const Lanes<G>& L) {
-  for_window_rows<G>(base, ld, L, [&](auto rc, float2 e) { t[decltype(rc)::value] = e; });
+  for_window_rows<G>(base, ld, col, L, [&](auto rc, float2 e) { t[decltype(rc)::value] = e; });
 }
 // Adds g (layout A) into the complex gradient rows.  permlane32_swap pairs
 // lanes l and l+32 so that each atomic instruction covers 32 consecutive
-// complex values (256 contiguous bytes) instead of every other float of 64.
+// complex values (256 contiguous bytes) instead of every other float of 64;
+// with the window's roll they are two whole 128-byte lines (except where the
+// window wraps), which is what the memory side's atomic rate counts.
 template <class G>
-__device__ __forceinline__ void scatter_add(float2* __restrict__ gbase, long long gld, const float2 (&g)[G::R],
-                                            const Lanes<G>& L) {
+__device__ __forceinline__ void scatter_add(float2* __restrict__ gbase, long long gld, int roll,
+                                            const float2 (&g)[G::R], const Lanes<G>& L) {
   const int lane = L.tid & 63;
-  const int xb = L.x - lane;  // first column of this wave's 64 columns (uniform)
-  const int off0 = 2 * (lane & 31) + (lane >> 5);
+  const int x0 = L.x - lane + (lane & 31);  // slot columns of the two instructions: x0 and x0 + 32
+  const int off0 = 2 * window_col<G>(x0, roll) + (lane >> 5);
+  const int off1 = 2 * window_col<G>(x0 + 32, roll) + (lane >> 5);
   const int gldz = static_cast<int>(gld) + opaque_zero();
-  gbase += static_cast<long long>(L.n2) * gldz + xb;
+  gbase += static_cast<long long>(L.n2) * gldz;
   sfor<G::R>([&](auto rc) {
     constexpr int r = decltype(rc)::value;
     auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(g[r].x), __float_as_uint(g[r].y), false, false);
     float* __restrict__ row = reinterpret_cast<float*>(gbase + static_cast<long long>(r * G::Y2 * gldz));
     unsafeAtomicAdd(row + off0, __uint_as_float(sw[0]));
-    unsafeAtomicAdd(row + 64 + off0, __uint_as_float(sw[1]));
+    unsafeAtomicAdd(row + off1, __uint_as_float(sw[1]));
   });
 }
 
@@ -295,8 +325,30 @@ struct PositionJob {
   long long gld, gslice;
   float gscale;          // 2 x the upstream gradient factor
   int ck;                // checkpoint interval of the incident waves (1: all kept)
-  float2* probe_part;    // probe-gradient mode: this workgroup's partial sum (layout A)
+  float2* probe_part;    // probe-gradient mode: this workgroup's partial sum (layout A, window columns)
+  int roll;              // columns the window is rolled by (window_roll)
+  bool lines;            // 128-windows: stage the gradient and align its atomics row by row (scatter_add_lines)
 };
+
+// The roll of a position's window: aligned to the gradient where there is one
+// (its atomics are the memory side's bound), to the object otherwise.  Rows
+// with different offsets from a line (a pitch that is no multiple of 16) have
+// no common roll: 128-windows then stage the gradient in LDS and align every
+// row on its own.  Against staging always, the roll (with the runs of
+// job_position) took 16632 16-slice positions on 2048^2 from 38.1 to 35.9 ms
+// and 4096 eight-slice ones on 1024^2 from 5.10 to 4.50 ms: no LDS round trip
+// and two barriers less per slice; without staging or roll the same atomics
+// touch a third more lines (4 % slower than staging).
+template <class G, bool GRAD>
+__device__ __forceinline__ void set_roll(PositionJob& jb) {
+  if constexpr (GRAD) {
+    jb.lines = (jb.gld & 15) != 0 || (jb.S > 1 && (jb.gslice & 15) != 0);
+    jb.roll = window_roll(jb.grad, jb.gld, jb.gslice, jb.S);
+  } else {
+    jb.lines = false;
+    jb.roll = window_roll(jb.win, jb.ld, jb.sstride, jb.S);
+  }
+}
 
 // Per-workgroup state shared by all positions a workgroup processes.
 template <class G>
@@ -322,11 +374,10 @@ __device__ __forceinline__ float2 load_propagator(Shared<G>& sh, const float2* _
 // and for the gradient mode the adjoint sweep with the scatter-add.  Returns
 // the position loss in thread 0 (LOSS modes).  Starts and ends at a point where
 // every LDS read of the previous position has completed.
-// LINES: gradient atomics staged through LDS and aligned to 128-byte lines
-// (scatter_add_lines); otherwise lanes are paired in registers (scatter_add).
-// The staging costs an LDS round trip and two barriers per slice, which pays
-// off for 128-windows over many slices (the tile walk) but not for 64-windows
-// or the short slice stacks of the batched launch.
+// LINES: gradients whose rows have no common line offset (jb.lines) are staged
+// through LDS and aligned row by row (scatter_add_lines); all others, and all
+// 64-windows, are added from registers (scatter_add).  The staging costs an LDS
+// round trip and two barriers per slice, which pays off for 128-windows only.
 // AHEAD: the adjoint sweep requests each stored incident wave one propagation
 // early (measured faster in the position-parallel launch, no faster in the
 // batched one).
@@ -351,10 +402,11 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
     const int k = s == seg ? s / ck - 1 : nck + (s - seg - 1);
     return ws + static_cast<long long>(k + opaque_zero()) * (G::M * G::M);
   };
+  const int col = window_col<G>(L.x, jb.roll);
   float2 v[G::R];
   float2 t[G::R];  // the next slice's transmission window, loaded one propagation ahead
-  load_window<G>(v, jb.probe, G::M, L);
-  load_window<G>(t, jb.win, jb.ld, L);
+  load_window<G>(v, jb.probe, G::M, col, L);
+  load_window<G>(t, jb.win, jb.ld, col, L);
   for (int s = 0; s < S; ++s) {
     if (GRAD && s >= 1 && (s % ck == 0 || s > last)) {
       float2* __restrict__ w = wave_slot(s, s % ck == 0 ? s : last);
@@ -363,7 +415,7 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
     __builtin_amdgcn_sched_barrier(0);
     sfor<G::R>([&](auto rc) { v[decltype(rc)::value] = cmul(v[decltype(rc)::value], t[decltype(rc)::value]); });
     if (s + 1 < S) {
-      load_window<G>(t, jb.win + (s + 1) * jb.sstride, jb.ld, L);  // in flight during the propagation
+      load_window<G>(t, jb.win + (s + 1) * jb.sstride, jb.ld, col, L);  // in flight during the propagation
       // after the first slice the buffer was last read by the previous propagation's layout-A reads,
       // the slots each thread writes first
       propagate<G, false>(v, sh.lds, sh.hx, twb, hy, L, s > 0);
@@ -432,20 +484,22 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
   auto adjoint_step = [&](int s, int seg) {
     if (s == 0) {
       if constexpr (MODE == kModeLossGradProbe) {
-        // dF/dP += chi_0 conj(t_0[window]) into this workgroup's partial sum (only this
-        // thread touches these elements, so a plain read-modify-write is race-free)
-        load_window<G>(g, jb.win, jb.ld, L);
+        // dF/dP += chi_0 conj(t_0[window]) into this workgroup's partial sum: one thread per
+        // pixel within a position, and the barriers between positions order the threads that
+        // take a pixel in turn, so a plain read-modify-write is race-free
+        load_window<G>(g, jb.win, jb.ld, col, L);
         float2* __restrict__ pp = jb.probe_part + opaque_zero();
         float2 acc[G::R];
-        sfor<G::R>([&](auto rc) { acc[decltype(rc)::value] = pp[decltype(rc)::value * G::T + L.tid]; });
+        const int px = L.n2 * G::M + col;
+        sfor<G::R>([&](auto rc) { acc[decltype(rc)::value] = pp[decltype(rc)::value * G::T + px]; });
         __builtin_amdgcn_sched_barrier(0);
         sfor<G::R>([&](auto rc) {
           constexpr int r = decltype(rc)::value;
-          pp[r * G::T + L.tid] = cadd(acc[r], cmulc(v[r], g[r]));
+          pp[r * G::T + px] = cadd(acc[r], cmulc(v[r], g[r]));
         });
         __builtin_amdgcn_sched_barrier(0);
       }
-      load_window<G>(g, jb.probe, G::M, L);
+      load_window<G>(g, jb.probe, G::M, col, L);
       __builtin_amdgcn_sched_barrier(0);
       sfor<G::R>([&](auto rc) { g[decltype(rc)::value] = cmulc(v[decltype(rc)::value], g[decltype(rc)::value]); });
     } else {
@@ -453,7 +507,7 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
         const float2* __restrict__ w = wave_slot(s, seg);
         load_slot<G::R, G::T>(g, w, L.tid);
       }
-      load_window<G>(t, jb.win + s * jb.sstride, jb.ld, L);
+      load_window<G>(t, jb.win + s * jb.sstride, jb.ld, col, L);
       __builtin_amdgcn_sched_barrier(0);
       sfor<G::R>([&](auto rc) {
         constexpr int r = decltype(rc)::value;
@@ -462,25 +516,28 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
       });
     }
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (LINES) {
+    bool staged = false;
+    if constexpr (LINES) staged = jb.lines;
+    if (staged) {
       // no barrier: the last LDS access before this was the layout-A read that ends every transform,
       // of the slots each thread now writes
       e1_write_a<G>(sh.lds + opaque_zero(), g, L.n2, L.x);
       __syncthreads();
       scatter_add_lines<G>(jb.grad + s * jb.gslice, jb.gld, sh.lds, L);
     } else {
-      scatter_add<G>(jb.grad + s * jb.gslice, jb.gld, g, L);
+      scatter_add<G>(jb.grad + s * jb.gslice, jb.gld, jb.roll, g, L);
     }
     if (s > 0) {
+      // without staging, the buffer was last read by the layout-A reads of the previous transform
       if constexpr (!AHEAD) {
-        propagate<G, true>(v, sh.lds, sh.hx, twb, hy, L);
+        propagate<G, true>(v, sh.lds, sh.hx, twb, hy, L, !staged);
       } else {
         // psi_{s-1} is in the store now if it belongs to this segment or is a checkpoint (the inner
         // waves of an earlier segment are recomputed first); slice 0 takes the probe at its own step
         const int s1 = s - 1;
         const bool nxt = s1 >= 1 && (s1 >= seg || s1 % ck == 0);
         const float2* __restrict__ nw = nxt ? wave_slot(s1, s1 >= seg ? seg : s1) : ws;
-        propagate<G, true>(v, sh.lds, sh.hx, twb, hy, L, false, [&]() {
+        propagate<G, true>(v, sh.lds, sh.hx, twb, hy, L, !staged, [&]() {
           // both branches define g, so it is not live across the propagation
           if (nxt) {
             load_slot<G::R, G::T>(g, nw, L.tid);
@@ -503,13 +560,13 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
                                              (G::M * G::M);
         store_slot<G::R, G::T>(park, v, L.tid);
         if (seg == 0) {
-          load_window<G>(v, jb.probe, G::M, L);
+          load_window<G>(v, jb.probe, G::M, col, L);
         } else {
           const float2* __restrict__ w = wave_slot(seg, seg);
           load_slot<G::R, G::T>(v, w, L.tid);
         }
         for (int s = seg; s + 1 < seg_end; ++s) {
-          load_window<G>(t, jb.win + s * jb.sstride, jb.ld, L);
+          load_window<G>(t, jb.win + s * jb.sstride, jb.ld, col, L);
           __builtin_amdgcn_sched_barrier(0);
           sfor<G::R>([&](auto rc) { v[decltype(rc)::value] = cmul(v[decltype(rc)::value], t[decltype(rc)::value]); });
           propagate<G, false>(v, sh.lds, sh.hx, twb, hy, L);
@@ -566,7 +623,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
   }
 
   for (int j = 0;; ++j) {
-    const int p = job_position(j, a.n, static_cast<int>(gridDim.x));
+    const int p = job_position(j, a.n, static_cast<int>(gridDim.x), a.run);
     if (p < 0) break;
     const int gy = a.pos[2 * p], gx = a.pos[2 * p + 1];
     const int y0 = gy - a.oy, x0 = gx - a.ox;
@@ -605,6 +662,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
     jb.probe = a.probe + static_cast<long long>(p) * a.probe_stride;
     jb.meas = a.meas + static_cast<long long>(p) * (G::M * G::M);
     jb.intens = a.intens + static_cast<long long>(p) * (G::M * G::M);
+    set_roll<G, (MODE == kModeLossGrad || MODE == kModeLossGradProbe)>(jb);
     const double f = run_position<G, MODE, G::M == 128, true, true>(jb, sh, twb, hy, ws, L);
     if (LOSS && L.tid == 0) {
       a.loss_work[p] = f;
@@ -669,6 +727,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) batch_kernel(Batc
     jb.gslice = R.slice_stride;
     jb.gscale = 2.0f;
     jb.ck = 1;
+    set_roll<G, true>(jb);
     const double f = run_position<G, kModeLossGrad, G::M == 128>(jb, sh, twb, hy, ws, L);
     if (L.tid == 0) a.item_loss[item] = f;
   }
@@ -911,7 +970,7 @@ __global__ void __launch_bounds__(Geo<M>::T) shift_probe_kernel(const float2* __
   float2 twb[G::X1];
   load_twb<G>(twb, tw, L.m2);
   float2 v[G::R];
-  load_window<G>(v, probe, G::M, L);
+  load_window<G>(v, probe, G::M, L.x, L);
   dft2_a_to_c<G>(v, lds, twb, L);
   const float dy = shifts[2 * p], dx = shifts[2 * p + 1];
   const int qy = L.ky < M / 2 ? L.ky : L.ky - M;
@@ -948,7 +1007,19 @@ hipError_t launch_shift_probes(const float2* probe, const float* shifts, int n, 
   return hipGetLastError();
 }
 
-hipError_t launch_fused(const KernelArgs& a, int mode, int grid, hipStream_t st) {
+// Consecutive positions per workgroup (job_position).  Runs of 8 measured best while object and gradient fit
+// the 256 MiB Infinity Cache; beyond, the windows in flight on an XCD have to share what its L2 keeps, and
+// runs of 2 did.  Runs of 1 / 2 / 4 / 8 / 16: 4096 eight-slice positions on 1024^2 5.58 / 4.67 / 4.54 / 4.50 /
+// 4.57 ms, two slices 1.52 / 1.35 / 1.26 / 1.22 / 1.25 ms; 16632 16-slice positions on 2048^2 36.4 / 36.2 /
+// 36.5 / 36.9 / 37.8 ms.
+static int launch_run(const KernelArgs& a) {
+  const long long bytes = 2LL * a.S * a.bh * a.bw * static_cast<long long>(sizeof(float2));
+  return bytes <= (256LL << 20) ? 8 : 2;
+}
+
+hipError_t launch_fused(const KernelArgs& args, int mode, int grid, hipStream_t st) {
+  KernelArgs a = args;
+  a.run = launch_run(a);
   if (a.M == 128) return launch_fused_m<128>(a, mode, grid, st);
   if (a.M == 64) return launch_fused_m<64>(a, mode, grid, st);
   return hipErrorInvalidValue;
