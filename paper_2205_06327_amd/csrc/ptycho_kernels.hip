@@ -13,8 +13,8 @@
 // workspace in HBM (all of them, or checkpoints from which the adjoint sweep
 // recomputes the rest) and re-read in reverse order by the adjoint sweep.
 // Gradient windows are added to the caller's gradient with hardware float
-// atomics; the windows are held rolled to the gradient's 128-byte lines, so
-// each instruction covers two whole lines.  Optional
+// atomics; the lanes are rolled to the gradient's 128-byte lines, so each
+// instruction covers two whole lines.  Optional
 // outputs: the probe gradient (per-workgroup partial sums).
 #include "fft_lds.hpp"
 #include "ptycho_kernels.h"
@@ -88,7 +88,7 @@ __device__ __forceinline__ int job_position(int j, int n, int grid, int run) {
 
 template <class G>
 struct Lanes {
-  int tid, n2, x;       // layout A
+  int tid, n2, x;       // layout A; x: the window column of the lane (set_columns)
   int k1, m2;           // layout B
   int ky, jh;           // layout C
   __device__ __forceinline__ Lanes() {
@@ -182,54 +182,38 @@ __device__ __forceinline__ void idft2_c_to_a(float2 (&v)[G::R], float2* lds, con
   pass_a_inv<G>(v, L.n2);
 }
 
-// Windows are held rolled along x: lane x of layout A holds window column
-// (x - roll) mod M, `col` below.  A cyclic shift of the wave multiplies its DFT
-// by a unit-modulus ramp along kx, so it commutes with the propagator and
-// leaves |Psi| and the real factor that the residual puts on Psi unchanged:
-// the sweeps need nothing but the same roll in every load and store.  The roll
-// is the window's offset from a 128-byte line (window_roll), so that lanes
-// x = 16k .. 16k+15 access whole lines of the object and of the gradient
-// wherever the window starts.
-__device__ __forceinline__ int window_roll(const float2* origin, long long ld, long long sstride, int S) {
-  const bool same = (ld & 15) == 0 && (S == 1 || (sstride & 15) == 0);  // one offset for all rows
-  return same ? static_cast<int>((reinterpret_cast<unsigned long long>(origin) >> 3) & 15) : 0;
-}
-template <class G>
-__device__ __forceinline__ int window_col(int x, int roll) {
-  return (x - roll) & (G::M - 1);
-}
-// Window of the current position in layout A: row y = Y2*r + n2, column col.
+// Window of the current position in layout A: row y = Y2*r + n2, column x.
 // `base` is uniform across the workgroup; each row pointer is computed on the
 // scalar unit and the lane offset is the column, so the loads use the
 // scalar-base + 32-bit lane-offset addressing form.
 template <class G, class F>
-__device__ __forceinline__ void for_window_rows(const float2* __restrict__ base, long long ld, int col,
-                                                const Lanes<G>& L, F&& f) {
+__device__ __forceinline__ void for_window_rows(const float2* __restrict__ base, long long ld, const Lanes<G>& L,
+                                                F&& f) {
   const int ldz = static_cast<int>(ld) + opaque_zero();
   base += static_cast<long long>(L.n2) * ldz;
   sfor<G::R>([&](auto rc) {
     constexpr int r = decltype(rc)::value;
     const float2* __restrict__ row = base + static_cast<long long>(r * G::Y2 * ldz);
-    f(rc, row[col]);
+    f(rc, row[L.x]);
   });
 }
 template <class G>
-__device__ __forceinline__ void load_window(float2 (&t)[G::R], const float2* __restrict__ base, long long ld, int col,
+__device__ __forceinline__ void load_window(float2 (&t)[G::R], const float2* __restrict__ base, long long ld,
                                             const Lanes<G>& L) {
-  for_window_rows<G>(base, ld, col, L, [&](auto rc, float2 e) { t[decltype(rc)::value] = e; });
+  for_window_rows<G>(base, ld, L, [&](auto rc, float2 e) { t[decltype(rc)::value] = e; });
 }
 // Adds g (layout A) into the complex gradient rows.  permlane32_swap pairs
 // lanes l and l+32 so that each atomic instruction covers 32 consecutive
 // complex values (256 contiguous bytes) instead of every other float of 64;
-// with the window's roll they are two whole 128-byte lines (except where the
+// with the lanes rolled they are two whole 128-byte lines (except where the
 // window wraps), which is what the memory side's atomic rate counts.
 template <class G>
-__device__ __forceinline__ void scatter_add(float2* __restrict__ gbase, long long gld, int roll,
-                                            const float2 (&g)[G::R], const Lanes<G>& L) {
-  const int lane = L.tid & 63;
-  const int x0 = L.x - lane + (lane & 31);  // slot columns of the two instructions: x0 and x0 + 32
-  const int off0 = 2 * window_col<G>(x0, roll) + (lane >> 5);
-  const int off1 = 2 * window_col<G>(x0 + 32, roll) + (lane >> 5);
+__device__ __forceinline__ void scatter_add(float2* __restrict__ gbase, long long gld, const float2 (&g)[G::R],
+                                            const Lanes<G>& L) {
+  const int half = (L.tid >> 5) & 1;
+  const int x0 = L.x - 32 * half;  // the columns of the two instructions: x0 and x0 + 32, wrapped
+  const int off0 = 2 * (x0 & (G::M - 1)) + half;
+  const int off1 = 2 * ((x0 + 32) & (G::M - 1)) + half;
   const int gldz = static_cast<int>(gld) + opaque_zero();
   gbase += static_cast<long long>(L.n2) * gldz;
   sfor<G::R>([&](auto rc) {
@@ -326,12 +310,14 @@ struct PositionJob {
   float gscale;          // 2 x the upstream gradient factor
   int ck;                // checkpoint interval of the incident waves (1: all kept)
   float2* probe_part;    // probe-gradient mode: this workgroup's partial sum (layout A, window columns)
-  int roll;              // columns the window is rolled by (window_roll)
   bool lines;            // 128-windows: stage the gradient and align its atomics row by row (scatter_add_lines)
 };
 
-// The roll of a position's window: aligned to the gradient where there is one
-// (its atomics are the memory side's bound), to the object otherwise.  Rows
+// Which window column each layout-A lane holds.  Nothing in the transforms
+// depends on it (layout A only exchanges whole columns through LDS), so the
+// lanes are rolled by the gradient window's offset from a 128-byte line: lanes
+// 16k .. 16k+15 then add to whole lines wherever the window starts.  The values
+// and their order of summation are those of unrolled lanes, bit for bit.  Rows
 // with different offsets from a line (a pitch that is no multiple of 16) have
 // no common roll: 128-windows then stage the gradient in LDS and align every
 // row on its own.  Against staging always, the roll (with the runs of
@@ -339,15 +325,14 @@ struct PositionJob {
 // and 4096 eight-slice ones on 1024^2 from 5.10 to 4.50 ms: no LDS round trip
 // and two barriers less per slice; without staging or roll the same atomics
 // touch a third more lines (4 % slower than staging).
+// Without a gradient the object's lines decide.
 template <class G, bool GRAD>
-__device__ __forceinline__ void set_roll(PositionJob& jb) {
-  if constexpr (GRAD) {
-    jb.lines = (jb.gld & 15) != 0 || (jb.S > 1 && (jb.gslice & 15) != 0);
-    jb.roll = window_roll(jb.grad, jb.gld, jb.gslice, jb.S);
-  } else {
-    jb.lines = false;
-    jb.roll = window_roll(jb.win, jb.ld, jb.sstride, jb.S);
-  }
+__device__ __forceinline__ void set_columns(PositionJob& jb, Lanes<G>& L) {
+  const float2* origin = GRAD ? jb.grad : jb.win;
+  const long long ld = GRAD ? jb.gld : jb.ld, slice = GRAD ? jb.gslice : jb.sstride;
+  jb.lines = (ld & 15) != 0 || (jb.S > 1 && (slice & 15) != 0);
+  const int roll = jb.lines ? 0 : static_cast<int>((reinterpret_cast<unsigned long long>(origin) >> 3) & 15);
+  L.x = (L.tid - roll) & (G::M - 1);
 }
 
 // Per-workgroup state shared by all positions a workgroup processes.
@@ -402,11 +387,10 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
     const int k = s == seg ? s / ck - 1 : nck + (s - seg - 1);
     return ws + static_cast<long long>(k + opaque_zero()) * (G::M * G::M);
   };
-  const int col = window_col<G>(L.x, jb.roll);
   float2 v[G::R];
   float2 t[G::R];  // the next slice's transmission window, loaded one propagation ahead
-  load_window<G>(v, jb.probe, G::M, col, L);
-  load_window<G>(t, jb.win, jb.ld, col, L);
+  load_window<G>(v, jb.probe, G::M, L);
+  load_window<G>(t, jb.win, jb.ld, L);
   for (int s = 0; s < S; ++s) {
     if (GRAD && s >= 1 && (s % ck == 0 || s > last)) {
       float2* __restrict__ w = wave_slot(s, s % ck == 0 ? s : last);
@@ -415,7 +399,7 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
     __builtin_amdgcn_sched_barrier(0);
     sfor<G::R>([&](auto rc) { v[decltype(rc)::value] = cmul(v[decltype(rc)::value], t[decltype(rc)::value]); });
     if (s + 1 < S) {
-      load_window<G>(t, jb.win + (s + 1) * jb.sstride, jb.ld, col, L);  // in flight during the propagation
+      load_window<G>(t, jb.win + (s + 1) * jb.sstride, jb.ld, L);  // in flight during the propagation
       // after the first slice the buffer was last read by the previous propagation's layout-A reads,
       // the slots each thread writes first
       propagate<G, false>(v, sh.lds, sh.hx, twb, hy, L, s > 0);
@@ -487,10 +471,10 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
         // dF/dP += chi_0 conj(t_0[window]) into this workgroup's partial sum: one thread per
         // pixel within a position, and the barriers between positions order the threads that
         // take a pixel in turn, so a plain read-modify-write is race-free
-        load_window<G>(g, jb.win, jb.ld, col, L);
+        load_window<G>(g, jb.win, jb.ld, L);
         float2* __restrict__ pp = jb.probe_part + opaque_zero();
         float2 acc[G::R];
-        const int px = L.n2 * G::M + col;
+        const int px = L.n2 * G::M + L.x;
         sfor<G::R>([&](auto rc) { acc[decltype(rc)::value] = pp[decltype(rc)::value * G::T + px]; });
         __builtin_amdgcn_sched_barrier(0);
         sfor<G::R>([&](auto rc) {
@@ -499,7 +483,7 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
         });
         __builtin_amdgcn_sched_barrier(0);
       }
-      load_window<G>(g, jb.probe, G::M, col, L);
+      load_window<G>(g, jb.probe, G::M, L);
       __builtin_amdgcn_sched_barrier(0);
       sfor<G::R>([&](auto rc) { g[decltype(rc)::value] = cmulc(v[decltype(rc)::value], g[decltype(rc)::value]); });
     } else {
@@ -507,7 +491,7 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
         const float2* __restrict__ w = wave_slot(s, seg);
         load_slot<G::R, G::T>(g, w, L.tid);
       }
-      load_window<G>(t, jb.win + s * jb.sstride, jb.ld, col, L);
+      load_window<G>(t, jb.win + s * jb.sstride, jb.ld, L);
       __builtin_amdgcn_sched_barrier(0);
       sfor<G::R>([&](auto rc) {
         constexpr int r = decltype(rc)::value;
@@ -525,7 +509,7 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
       __syncthreads();
       scatter_add_lines<G>(jb.grad + s * jb.gslice, jb.gld, sh.lds, L);
     } else {
-      scatter_add<G>(jb.grad + s * jb.gslice, jb.gld, jb.roll, g, L);
+      scatter_add<G>(jb.grad + s * jb.gslice, jb.gld, g, L);
     }
     if (s > 0) {
       // without staging, the buffer was last read by the layout-A reads of the previous transform
@@ -560,13 +544,13 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
                                              (G::M * G::M);
         store_slot<G::R, G::T>(park, v, L.tid);
         if (seg == 0) {
-          load_window<G>(v, jb.probe, G::M, col, L);
+          load_window<G>(v, jb.probe, G::M, L);
         } else {
           const float2* __restrict__ w = wave_slot(seg, seg);
           load_slot<G::R, G::T>(v, w, L.tid);
         }
         for (int s = seg; s + 1 < seg_end; ++s) {
-          load_window<G>(t, jb.win + s * jb.sstride, jb.ld, col, L);
+          load_window<G>(t, jb.win + s * jb.sstride, jb.ld, L);
           __builtin_amdgcn_sched_barrier(0);
           sfor<G::R>([&](auto rc) { v[decltype(rc)::value] = cmul(v[decltype(rc)::value], t[decltype(rc)::value]); });
           propagate<G, false>(v, sh.lds, sh.hx, twb, hy, L);
@@ -599,7 +583,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
   using G = Geo<M>;
   constexpr bool LOSS = MODE != kModeIntensity;
   __shared__ Shared<G> sh;
-  const Lanes<G> L;
+  Lanes<G> L;
   float2 twb[G::X1];
   load_twb<G>(twb, a.tw, L.m2);
   const float2 hy = load_propagator<G>(sh, a.h, L);
@@ -628,6 +612,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
     const int gy = a.pos[2 * p], gx = a.pos[2 * p + 1];
     const int y0 = gy - a.oy, x0 = gx - a.ox;
     bool ok;
+    jb.win = a.obj + static_cast<long long>(y0) * a.ld + x0;
     if (a.tiles != nullptr) {  // all-tiles mode: the owning tile's box and gradient buffer (uniform)
       const int tk = a.tile_of_pos[p];
       ok = tk >= 0 && tk < a.ntiles;
@@ -658,11 +643,10 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
       }
       continue;
     }
-    jb.win = a.obj + static_cast<long long>(y0) * a.ld + x0;
     jb.probe = a.probe + static_cast<long long>(p) * a.probe_stride;
     jb.meas = a.meas + static_cast<long long>(p) * (G::M * G::M);
     jb.intens = a.intens + static_cast<long long>(p) * (G::M * G::M);
-    set_roll<G, (MODE == kModeLossGrad || MODE == kModeLossGradProbe)>(jb);
+    set_columns<G, (MODE == kModeLossGrad || MODE == kModeLossGradProbe)>(jb, L);
     const double f = run_position<G, MODE, G::M == 128, true, true>(jb, sh, twb, hy, ws, L);
     if (LOSS && L.tid == 0) {
       a.loss_work[p] = f;
@@ -681,7 +665,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) batch_kernel(Batc
   using G = Geo<M>;
   __shared__ Shared<G> sh;
   __shared__ int job;
-  const Lanes<G> L;
+  Lanes<G> L;
   float2 twb[G::X1];
   load_twb<G>(twb, a.tw, L.m2);
   float2* __restrict__ ws = a.ws + static_cast<long long>(blockIdx.x) * ws_slots(a.smax, 1) * (G::M * G::M);
@@ -727,7 +711,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) batch_kernel(Batc
     jb.gslice = R.slice_stride;
     jb.gscale = 2.0f;
     jb.ck = 1;
-    set_roll<G, true>(jb);
+    set_columns<G, true>(jb, L);
     const double f = run_position<G, kModeLossGrad, G::M == 128>(jb, sh, twb, hy, ws, L);
     if (L.tid == 0) a.item_loss[item] = f;
   }
@@ -970,7 +954,7 @@ __global__ void __launch_bounds__(Geo<M>::T) shift_probe_kernel(const float2* __
   float2 twb[G::X1];
   load_twb<G>(twb, tw, L.m2);
   float2 v[G::R];
-  load_window<G>(v, probe, G::M, L.x, L);
+  load_window<G>(v, probe, G::M, L);
   dft2_a_to_c<G>(v, lds, twb, L);
   const float dy = shifts[2 * p], dx = shifts[2 * p + 1];
   const int qy = L.ky < M / 2 ? L.ky : L.ky - M;
