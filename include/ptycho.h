@@ -427,6 +427,66 @@ int ptycho_box_exchange(ptycho_ctx* ctx, int32_t S, const void* src, int32_t sy0
                         int32_t dh, int32_t dw, int64_t d_slice_stride, int32_t d_ld, uint32_t mode);
 
 /*
+ * Whole tile grids in one call.  A ptycho_tile_desc names a tile, its extended
+ * box and a buffer on it (`grad`, device complex64 [S][eh][ew], dense; S of the
+ * context); the buffers must not share memory (E_ARG).  At most 4096 tiles.
+ * Sums run in a fixed order.  Stream-ordered; allocate nothing.
+ *
+ * ptycho_tiles_stitch: out (complex64, element (s, y, x) at
+ * out[s*out_slice_stride + y*out_ld + x]) from the tiles, which must cover
+ * H x W without overlap (E_SHAPE):
+ *   PTYCHO_STITCH_SUM:      the sum, in tile order, of the buffers whose boxes
+ *                           hold a pixel: ptycho_zero_gradient and then
+ *                           ptycho_tile_accumulate for every tile;
+ *   PTYCHO_STITCH_INTERIOR: each tile's own pixels (the final stitch of Alg. 1).
+ *
+ * ptycho_tiles_neighbour_add: Section III's exchange.  dst[k] (layout of tile
+ * k's buffer) = tile k's buffer plus, on the overlaps, those of its up to eight
+ * neighbours in the tiles_y x tiles_x grid (row-major), in row-major order.
+ *
+ * ptycho_tiles_passes: Section IV's directional passes between the buffers, in
+ * place: down each column add, up replace, along each row add, back replace.
+ */
+#define PTYCHO_STITCH_SUM 0u
+#define PTYCHO_STITCH_INTERIOR 1u
+int ptycho_tiles_stitch(ptycho_ctx* ctx, const ptycho_tile_desc* tiles, int32_t ntiles, int32_t H, int32_t W,
+                        void* out, int64_t out_slice_stride, int32_t out_ld, uint32_t mode);
+int ptycho_tiles_neighbour_add(ptycho_ctx* ctx, const ptycho_tile_desc* tiles, void* const* dst, int32_t tiles_y,
+                               int32_t tiles_x);
+int ptycho_tiles_passes(ptycho_ctx* ctx, const ptycho_tile_desc* tiles, int32_t tiles_y, int32_t tiles_x);
+
+/*
+ * Alg. 1 on a grid of tiles.  Each tile keeps, on its extended box (dense
+ * complex64 [S][eh][ew], every buffer in its own memory): its object
+ * copy V, its accumulation buffer AccBuf and a gradient buffer that is zero
+ * between calls (the caller zeroes it once).
+ *
+ * ptycho_tiles_batch_step: one batch of every tile.  The batch is n indices
+ * into the `total` positions (pos, meas and tile_of_pos: device, `total`
+ * entries), grouped by tile: tile k owns index[segments[k] .. segments[k+1]);
+ * segments has ntiles + 1 entries, on the device and, the same values, on the
+ * host.  In order: the gradient of each tile's batch at its V;
+ * AccBuf += gradient, V -= step * gradient, gradient = 0; losses[k] (device)
+ * = the loss of tile k's batch.  Windows are checked on the device as by
+ * ptycho_tiles_grad.  n must not exceed the reserved capacity.
+ *
+ * ptycho_tiles_flush: the directional passes on the AccBufs, then
+ * V -= step * AccBuf and AccBuf = 0 for every tile.
+ */
+typedef struct ptycho_tile_state {
+  int32_t ty0, ty1, tx0, tx1; /* the tile, global pixels, half-open */
+  int32_t ey0, ex0, eh, ew;   /* its extended box */
+  void* obj;                  /* V */
+  void* acc;                  /* AccBuf */
+  void* grad;                 /* gradient of a batch, zero between calls */
+} ptycho_tile_state;
+int ptycho_tiles_batch_step(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int32_t ntiles, const int32_t* tile_of_pos,
+                            const void* probe, const int32_t* pos, const float* meas, int32_t total,
+                            const int32_t* index, int32_t n, const int32_t* segments, const int32_t* host_segments,
+                            float step, double* losses);
+int ptycho_tiles_flush(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int32_t tiles_y, int32_t tiles_x, float step);
+
+/*
  * ptycho_zero_gradient: sets S slices of an H x W complex64 array with the
  * given strides to zero on the context stream (the reset of a gradient or
  * accumulation buffer; a plain fill kernel, so it may be graph-captured).

@@ -36,6 +36,11 @@ class TileDesc(ctypes.Structure):
                 ("grad", ctypes.c_void_p)]
 
 
+class TileState(ctypes.Structure):
+    """ptycho_tile_state: a tile of Alg. 1 with its object copy, accumulation buffer and batch gradient."""
+    _fields_ = TileDesc._fields_[:8] + [("obj", ctypes.c_void_p), ("acc", ctypes.c_void_p), ("grad", ctypes.c_void_p)]
+
+
 EXPORTED = (
     "ptycho_create", "ptycho_destroy", "ptycho_set_stream", "ptycho_reserve", "ptycho_workspace_bytes",
     "ptycho_forward", "ptycho_loss_grad", "ptycho_tile_grad", "ptycho_bin_positions",
@@ -48,7 +53,8 @@ EXPORTED = (
     "ptycho_box_axpy", "ptycho_potential_transmission", "ptycho_potential_gradient", "ptycho_loss_grad_probe",
     "ptycho_copy_box", "ptycho_tiles_grad", "ptycho_shift_probes", "ptycho_forward_stack",
     "ptycho_loss_grad_stack", "ptycho_loss_stack", "ptycho_tiles_grad_stack", "ptycho_gd_step_size",
-    "ptycho_loss_grad_static",
+    "ptycho_loss_grad_static", "ptycho_tiles_stitch", "ptycho_tiles_neighbour_add", "ptycho_tiles_passes",
+    "ptycho_tiles_batch_step", "ptycho_tiles_flush",
 )
 
 
@@ -123,6 +129,14 @@ def lib() -> ctypes.CDLL:
                                                c_i32, c_vp, c_i32, c_i32, c_i32, c_i32, c_i64, c_i32]),
             "ptycho_box_exchange": (ctypes.c_int, [c_vp, c_i32, c_vp, c_i32, c_i32, c_i32, c_i32, c_i64, c_i32,
                                                    c_vp, c_i32, c_i32, c_i32, c_i32, c_i64, c_i32, c_u32]),
+            "ptycho_tiles_stitch": (ctypes.c_int, [c_vp, ctypes.POINTER(TileDesc), c_i32, c_i32, c_i32, c_vp, c_i64,
+                                                   c_i32, c_u32]),
+            "ptycho_tiles_neighbour_add": (ctypes.c_int, [c_vp, ctypes.POINTER(TileDesc), ctypes.POINTER(c_vp), c_i32,
+                                                          c_i32]),
+            "ptycho_tiles_passes": (ctypes.c_int, [c_vp, ctypes.POINTER(TileDesc), c_i32, c_i32]),
+            "ptycho_tiles_batch_step": (ctypes.c_int, [c_vp, ctypes.POINTER(TileState), c_i32, c_vp, c_vp, c_vp, c_vp,
+                                                       c_i32, c_vp, c_i32, c_vp, P_i32, ctypes.c_float, c_vp]),
+            "ptycho_tiles_flush": (ctypes.c_int, [c_vp, ctypes.POINTER(TileState), c_i32, c_i32, ctypes.c_float]),
             "ptycho_profile_read": (ctypes.c_int, [c_vp, ctypes.POINTER(c_dbl), ctypes.POINTER(c_i64),
                                                    ctypes.POINTER(c_i64)]),
             "ptycho_last_error": (ctypes.c_char_p, []),
@@ -652,6 +666,100 @@ def ptycho_tiles_grad(ctx: Context, obj, tiles, halo: int, tile_of_pos, probe, p
                                        c_vp(tile_of_pos.data_ptr()), c_vp(probe.data_ptr()), c_vp(pos.data_ptr()), n,
                                        c_vp(meas.data_ptr()), c_vp(loss.data_ptr()), lpp, flags))
     return loss
+
+
+def _tile_table(ctx: Context, tiles, name: str):
+    """ctypes array of (tile (ty0, ty1, tx0, tx1), box (ey0, ex0, eh, ew), complex64 [S, eh, ew] buffer)."""
+    torch = _torch()
+    arr = (TileDesc * len(tiles))()
+    for k, (tile, box, g) in enumerate(tiles):
+        _need(g, torch.complex64, (ctx.S, box[2], box[3]), f"{name} {k}")
+        arr[k] = TileDesc(*tile, *box, g.data_ptr())
+    return arr
+
+
+STITCH_SUM, STITCH_INTERIOR = 0, 1
+
+
+def ptycho_tiles_stitch(ctx: Context, tiles, out, mode: int = STITCH_SUM) -> None:
+    """out (complex64 [S, H, W], unit stride along W) from per-tile buffers in one launch: the sum of the
+    buffers whose boxes hold a pixel, or (STITCH_INTERIOR) each tile's own pixels.  tiles: sequence of
+    (tile (ty0, ty1, tx0, tx1), box (ey0, ex0, eh, ew), complex64 [S, eh, ew]) covering H x W."""
+    torch = _torch()
+    _on_device(out, "out")
+    if out.dtype != torch.complex64 or out.dim() != 3 or out.stride(2) != 1 or out.shape[0] != ctx.S:
+        raise ValueError("out must be complex64 [S, H, W] with unit stride along W")
+    arr = _tile_table(ctx, tiles, "tile buffer")
+    ctx._bind_stream()
+    _check(lib().ptycho_tiles_stitch(ctx.handle, arr, len(tiles), out.shape[1], out.shape[2], c_vp(out.data_ptr()),
+                                     out.stride(0), out.stride(1), mode))
+
+
+def ptycho_tiles_neighbour_add(ctx: Context, tiles, dst, grid: Tuple[int, int]) -> None:
+    """dst[k] = tile k's buffer plus its neighbours' on the overlaps, for every tile of the row-major grid
+    (Section III's exchange); dst: complex64 [S, eh, ew] buffers in separate memory."""
+    torch = _torch()
+    if len(tiles) != grid[0] * grid[1] or len(dst) != len(tiles):
+        raise ValueError("tiles and dst must have one entry per tile of the grid")
+    arr = _tile_table(ctx, tiles, "tile buffer")
+    ptrs = (c_vp * len(dst))()
+    for k, d in enumerate(dst):
+        _need(d, torch.complex64, (ctx.S, tiles[k][1][2], tiles[k][1][3]), f"destination {k}")
+        ptrs[k] = d.data_ptr()
+    ctx._bind_stream()
+    _check(lib().ptycho_tiles_neighbour_add(ctx.handle, arr, ptrs, int(grid[0]), int(grid[1])))
+
+
+def ptycho_tiles_passes(ctx: Context, tiles, grid: Tuple[int, int]) -> None:
+    """Section IV's directional passes between the buffers of a row-major grid of tiles, in place."""
+    if len(tiles) != grid[0] * grid[1]:
+        raise ValueError("tiles must have one entry per tile of the grid")
+    arr = _tile_table(ctx, tiles, "tile buffer")
+    ctx._bind_stream()
+    _check(lib().ptycho_tiles_passes(ctx.handle, arr, int(grid[0]), int(grid[1])))
+
+
+def tile_states(ctx: Context, tiles):
+    """ctypes array of (tile, box, V, AccBuf, gradient) for ptycho_tiles_batch_step / ptycho_tiles_flush."""
+    torch = _torch()
+    arr = (TileState * len(tiles))()
+    for k, (tile, box, *bufs) in enumerate(tiles):
+        for b in bufs:
+            _need(b, torch.complex64, (ctx.S, box[2], box[3]), f"tile {k} buffer")
+        arr[k] = TileState(*tile, *box, *(b.data_ptr() for b in bufs))
+    return arr
+
+
+def ptycho_tiles_batch_step(ctx: Context, tiles, tile_of_pos, probe, pos, meas, index, segments, host_segments,
+                            step: float, losses) -> None:
+    """One batch of Alg. 1 on every tile (see tile_states): index int32 [n] selects positions of pos
+    (int32 [total, 2]), meas and tile_of_pos, grouped by tile at segments (int32 [ntiles + 1], on the
+    device, and the same as a numpy array); losses float64 [ntiles] receives the batches' losses."""
+    torch = _torch()
+    M = ctx.M
+    total = _need_pos(pos)
+    _need(probe, torch.complex64, (M, M), "probe")
+    _need(meas, torch.float32, (total, M, M), "meas")
+    _need(tile_of_pos, torch.int32, (total,), "tile_of_pos")
+    _need(index, torch.int32, None, "index")
+    _need(segments, torch.int32, (len(tiles) + 1,), "segments")
+    _need(losses, torch.float64, (len(tiles),), "losses")
+    host = np.ascontiguousarray(host_segments, dtype=np.int32)
+    if host.shape != (len(tiles) + 1,):
+        raise ValueError("host_segments must have one entry per tile and one more")
+    ctx._bind_stream()
+    _check(lib().ptycho_tiles_batch_step(ctx.handle, tiles, len(tiles), c_vp(tile_of_pos.data_ptr()),
+                                         c_vp(probe.data_ptr()), c_vp(pos.data_ptr()), c_vp(meas.data_ptr()), total,
+                                         c_vp(index.data_ptr()), index.numel(), c_vp(segments.data_ptr()),
+                                         host.ctypes.data_as(P_i32), float(step), c_vp(losses.data_ptr())))
+
+
+def ptycho_tiles_flush(ctx: Context, tiles, grid: Tuple[int, int], step: float) -> None:
+    """The passes on every AccBuf, then V -= step * AccBuf and AccBuf = 0 (see tile_states)."""
+    if len(tiles) != grid[0] * grid[1]:
+        raise ValueError("tiles must have one entry per tile of the grid")
+    ctx._bind_stream()
+    _check(lib().ptycho_tiles_flush(ctx.handle, tiles, int(grid[0]), int(grid[1]), float(step)))
 
 
 def ptycho_copy_box(ctx: Context, src, dst) -> None:

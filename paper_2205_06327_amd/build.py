@@ -15,6 +15,7 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libptycho.so")
 SOURCES = [
     os.path.join(HERE, "csrc", "ptycho_kernels.hip"),
+    os.path.join(HERE, "csrc", "tile_kernels.hip"),
     os.path.join(HERE, "csrc", "ptycho_api.cpp"),
     os.path.join(HERE, "csrc", "ptycho_static.hip"),
 ]

@@ -105,6 +105,7 @@ struct ptycho_ctx {
   float2* d_probe_part = nullptr;  // probe-gradient partial sums, grid * M*M
   ptycho::TileDesc* d_tiles = nullptr;  // tile table of ptycho_tiles_grad (kMaxTiles entries)
   std::vector<ptycho::TileDesc> h_tiles;
+  size_t tiles_cap = ptycho::kMaxTiles;
   float2* d_ws = nullptr;  // incident-wave store, grid * ws_slots(S, ck) * M*M
   int ck = 1;              // checkpoint interval of the incident waves
   double* d_loss = nullptr;  // per-position losses [capacity]
@@ -593,6 +594,30 @@ int ptycho_tile_grad(ptycho_ctx* ctx, const void* obj_ext, int32_t ey0, int32_t 
 }  // extern "C"
 
 namespace {
+// The context's device tile table.  It is uploaded only when it changed (a walk passes the same tiles
+// every step).  The copy is stream-ordered after launches that still read the old table, and the host
+// copy it reads is kept unchanged until the stream has passed it.
+int upload_tiles(ptycho_ctx* ctx, std::vector<ptycho::TileDesc>& table) {
+  const bool same = ctx->h_tiles.size() == table.size() &&
+                    std::memcmp(ctx->h_tiles.data(), table.data(), table.size() * sizeof(ptycho::TileDesc)) == 0;
+  if (same) return PTYCHO_OK;
+  PT_HIP(hipStreamSynchronize(ctx->stream));  // the previous upload has been read
+  if (table.size() > ctx->tiles_cap) {  // only Alg. 1 takes more tiles than the context starts with
+    ptycho::TileDesc* d = nullptr;
+    const hipError_t e = hipMalloc(&d, table.size() * sizeof(ptycho::TileDesc));
+    if (e != hipSuccess) return fail(PTYCHO_E_NOMEM, "tile table: %s", hipGetErrorString(e));
+    ctx->h_tiles.clear();
+    PT_HIP(hipFree(ctx->d_tiles));
+    ctx->d_tiles = d;
+    ctx->bytes += static_cast<int64_t>((table.size() - ctx->tiles_cap) * sizeof(ptycho::TileDesc));
+    ctx->tiles_cap = table.size();
+  }
+  ctx->h_tiles.swap(table);
+  PT_HIP(hipMemcpyAsync(ctx->d_tiles, ctx->h_tiles.data(), ctx->h_tiles.size() * sizeof(ptycho::TileDesc),
+                        hipMemcpyHostToDevice, ctx->stream));
+  return PTYCHO_OK;
+}
+
 int tiles_grad_impl(ptycho_ctx* ctx, const void* obj, int32_t H, int32_t W, int64_t slice_stride, int32_t ld,
                     const ptycho_tile_desc* tiles, int32_t ntiles, int32_t halo, const int32_t* tile_of_pos,
                     const void* probe, int64_t probe_stride, const int32_t* pos, int32_t n, const float* meas,
@@ -630,17 +655,7 @@ int tiles_grad_impl(ptycho_ctx* ctx, const void* obj, int32_t H, int32_t W, int6
     d.gslice = static_cast<long long>(t.eh) * t.ew;
     d.gld = t.ew;
   }
-  // Upload the table only when it changed (a walk passes the same tiles every step).  The copy is
-  // stream-ordered after launches that still read the old table, and the host copy it reads is
-  // kept unchanged until the stream has passed it.
-  const bool same = ctx->h_tiles.size() == table.size() &&
-                    std::memcmp(ctx->h_tiles.data(), table.data(), table.size() * sizeof(ptycho::TileDesc)) == 0;
-  if (!same) {
-    PT_HIP(hipStreamSynchronize(ctx->stream));  // the previous upload has been read
-    ctx->h_tiles.swap(table);
-    PT_HIP(hipMemcpyAsync(ctx->d_tiles, ctx->h_tiles.data(), ntiles * sizeof(ptycho::TileDesc),
-                          hipMemcpyHostToDevice, ctx->stream));
-  }
+  if ((rc = upload_tiles(ctx, table)) != PTYCHO_OK) return rc;
   const bool acc = (flags & PTYCHO_ACCUMULATE) != 0;
   if (!acc) PT_HIP(ptycho::launch_zero_tiles(ctx->d_tiles, ntiles, ctx->S, ctx->stream));
   ptycho::KernelArgs a = base_args(ctx);
@@ -842,6 +857,329 @@ int ptycho_box_axpy(ptycho_ctx* ctx, int32_t S, float alpha, const void* src, in
                     int32_t dw, int64_t d_slice_stride, int32_t d_ld) {
   return box_combine(ctx, S, src, sy0, sx0, sh, sw, s_slice_stride, s_ld, dst, dy0, dx0, dh, dw, d_slice_stride, d_ld,
                      false, alpha);
+}
+
+}  // extern "C"
+
+// ---------------------------------------------------------------------------
+// whole tile grids: stitches, neighbour addition, directional passes, Alg. 1
+// ---------------------------------------------------------------------------
+namespace {
+
+struct Rect {  // half-open, global pixels
+  int y0, y1, x0, x1;
+  bool empty() const { return y0 >= y1 || x0 >= x1; }
+};
+Rect meet(const Rect& a, const Rect& b) {
+  return {std::max(a.y0, b.y0), std::min(a.y1, b.y1), std::max(a.x0, b.x0), std::min(a.x1, b.x1)};
+}
+Rect box_of(const ptycho_tile_desc& t) { return {t.ey0, t.ey0 + t.eh, t.ex0, t.ex0 + t.ew}; }
+Rect tile_of(const ptycho_tile_desc& t) { return {t.ty0, t.ty1, t.tx0, t.tx1}; }
+
+// Tiles with their buffers: the tile inside its box, the box inside H x W (when given), and each buffer
+// device memory of S * eh * ew values, no two of them sharing memory.
+int check_tiles(const ptycho_ctx* c, const ptycho_tile_desc* tiles, int32_t n, int32_t H, int32_t W) {
+  if (n < 1 || n > ptycho::kMaxTiles) return fail(PTYCHO_E_ARG, "tile count %d outside [1, %d]", n, ptycho::kMaxTiles);
+  for (int k = 0; k < n; ++k) {
+    const ptycho_tile_desc& t = tiles[k];
+    if (t.eh < 1 || t.ew < 1 || t.ey0 < 0 || t.ex0 < 0 || t.ey0 > INT32_MAX - t.eh || t.ex0 > INT32_MAX - t.ew ||
+        t.ty0 < t.ey0 || t.tx0 < t.ex0 || t.ty1 > t.ey0 + t.eh || t.tx1 > t.ex0 + t.ew || t.ty0 > t.ty1 ||
+        t.tx0 > t.tx1 || t.ey0 + t.eh > H || t.ex0 + t.ew > W)
+      return fail(PTYCHO_E_SHAPE, "tile %d: bad tile or box", k);
+    if (!t.grad) return fail(PTYCHO_E_ARG, "tile %d: null buffer", k);
+    PT_BUF(c->device, t.grad, static_cast<size_t>(c->S) * t.eh * t.ew * sizeof(float2), "tile buffer");
+  }
+  return PTYCHO_OK;
+}
+
+// The address ranges must be disjoint.
+int check_disjoint(std::vector<std::pair<uintptr_t, uintptr_t>>& r) {
+  std::sort(r.begin(), r.end());
+  for (size_t i = 1; i < r.size(); ++i)
+    if (r[i].first < r[i - 1].second) return fail(PTYCHO_E_ARG, "buffers share memory");
+  return PTYCHO_OK;
+}
+std::pair<uintptr_t, uintptr_t> range_of(const void* p, size_t elems) {
+  const uintptr_t b = reinterpret_cast<uintptr_t>(p);
+  return {b, b + elems * sizeof(float2)};
+}
+
+// Collects box operations into launches.  Operations of one stage are independent of each other.
+class BoxStage {
+ public:
+  explicit BoxStage(ptycho_ctx* c) : c_(c) { list_.nops = list_.nsrcs = 0; }
+  // dst over `at`, whose element (s, at.y0, at.x0) is at p
+  int begin(const Rect& at, float2* p, long long slice, long long ld, int init) {
+    if (list_.nops == ptycho::BoxList::kOps || list_.nsrcs == ptycho::BoxList::kSrcs) {
+      const int rc = flush();
+      if (rc != PTYCHO_OK) return rc;
+    }
+    at_ = at;
+    list_.op[list_.nops++] = {p, slice, ld, at.y1 - at.y0, at.x1 - at.x0, init, 0, list_.nsrcs};
+    return PTYCHO_OK;
+  }
+  // a source on `box`, whose element (s, box.y0, box.x0) is at p
+  int add(const Rect& box, const float2* p, long long slice, long long ld) {
+    const Rect m = meet(at_, box);
+    if (m.empty()) return PTYCHO_OK;
+    if (list_.nsrcs == ptycho::BoxList::kSrcs) {  // continue the operation in the next launch
+      ptycho::BoxOp o = list_.op[list_.nops - 1];
+      if (o.nsrc > 0) {
+        const int rc = flush();
+        if (rc != PTYCHO_OK) return rc;
+        o.init = ptycho::kBoxAdd;
+      } else {
+        --list_.nops;
+        const int rc = flush();
+        if (rc != PTYCHO_OK) return rc;
+      }
+      o.nsrc = 0;
+      o.first = 0;
+      list_.op[list_.nops++] = o;
+    }
+    const long long off = static_cast<long long>(at_.y0 - box.y0) * ld + (at_.x0 - box.x0);
+    list_.src[list_.nsrcs++] = {p + off, slice, ld, m.y0 - at_.y0, m.y1 - at_.y0, m.x0 - at_.x0, m.x1 - at_.x0};
+    ++list_.op[list_.nops - 1].nsrc;
+    return PTYCHO_OK;
+  }
+  int flush() {
+    int rows = 0;
+    for (int k = 0; k < list_.nops; ++k) rows = std::max(rows, list_.op[k].h);
+    if (rows > 0) PT_HIP(ptycho::launch_box_list(list_, c_->S, rows, c_->stream));
+    list_.nops = list_.nsrcs = 0;
+    return PTYCHO_OK;
+  }
+
+ private:
+  ptycho_ctx* c_;
+  ptycho::BoxList list_;
+  Rect at_{};
+};
+
+int add_tile(BoxStage& st, const ptycho_tile_desc& t) {
+  return st.add(box_of(t), static_cast<const float2*>(t.grad), static_cast<long long>(t.eh) * t.ew, t.ew);
+}
+
+// One exchange on the overlap of two tiles' boxes: dst += src, or dst = src.
+int exchange(BoxStage& st, const ptycho_tile_desc& src, const ptycho_tile_desc& dst, bool replace) {
+  const Rect m = meet(box_of(src), box_of(dst));
+  if (m.empty()) return PTYCHO_OK;
+  float2* p = static_cast<float2*>(dst.grad) + static_cast<long long>(m.y0 - dst.ey0) * dst.ew + (m.x0 - dst.ex0);
+  const int rc = st.begin(m, p, static_cast<long long>(dst.eh) * dst.ew, dst.ew,
+                          replace ? ptycho::kBoxCopy : ptycho::kBoxAdd);
+  return rc != PTYCHO_OK ? rc : add_tile(st, src);
+}
+
+// Section IV's passes, one launch (or more, for many tiles) per step along a direction: the exchanges of a
+// step run between different pairs of tile rows or columns' neighbours and touch disjoint destinations,
+// and each reads only buffers that the step does not write.
+int enqueue_passes(ptycho_ctx* ctx, const std::vector<ptycho_tile_desc>& t, int ny, int nx) {
+  int rc = PTYCHO_OK;
+  auto step = [&](int count, auto&& pair, bool replace) {
+    BoxStage st(ctx);
+    for (int i = 0; i < count && rc == PTYCHO_OK; ++i) {
+      const auto [src, dst] = pair(i);
+      rc = exchange(st, t[src], t[dst], replace);
+    }
+    if (rc == PTYCHO_OK) rc = st.flush();
+  };
+  for (int y = 0; y + 1 < ny && rc == PTYCHO_OK; ++y)
+    step(nx, [&](int x) { return std::make_pair(y * nx + x, (y + 1) * nx + x); }, false);
+  for (int y = ny - 1; y > 0 && rc == PTYCHO_OK; --y)
+    step(nx, [&](int x) { return std::make_pair(y * nx + x, (y - 1) * nx + x); }, true);
+  for (int x = 0; x + 1 < nx && rc == PTYCHO_OK; ++x)
+    step(ny, [&](int y) { return std::make_pair(y * nx + x, y * nx + x + 1); }, false);
+  for (int x = nx - 1; x > 0 && rc == PTYCHO_OK; --x)
+    step(ny, [&](int y) { return std::make_pair(y * nx + x, y * nx + x - 1); }, true);
+  return rc;
+}
+
+int check_grid(const ptycho_ctx* c, const ptycho_tile_desc* tiles, int32_t ny, int32_t nx) {
+  if (!c) return fail(PTYCHO_E_ARG, "null context");
+  if (!tiles || ny < 1 || nx < 1 || static_cast<int64_t>(ny) * nx > ptycho::kMaxTiles)
+    return fail(PTYCHO_E_ARG, "bad tile grid");
+  const int rc = check_tiles(c, tiles, ny * nx, INT32_MAX, INT32_MAX);
+  if (rc != PTYCHO_OK) return rc;
+  std::vector<std::pair<uintptr_t, uintptr_t>> r;
+  for (int k = 0; k < ny * nx; ++k)
+    r.push_back(range_of(tiles[k].grad, static_cast<size_t>(c->S) * tiles[k].eh * tiles[k].ew));
+  return check_disjoint(r);
+}
+
+}  // namespace
+
+extern "C" {
+
+int ptycho_tiles_stitch(ptycho_ctx* ctx, const ptycho_tile_desc* tiles, int32_t ntiles, int32_t H, int32_t W,
+                        void* out, int64_t out_slice_stride, int32_t out_ld, uint32_t mode) {
+  if (!ctx) return fail(PTYCHO_E_ARG, "null context");
+  if (!tiles || !out) return fail(PTYCHO_E_ARG, "null pointer argument");
+  if (mode != PTYCHO_STITCH_SUM && mode != PTYCHO_STITCH_INTERIOR) return fail(PTYCHO_E_ARG, "bad mode %u", mode);
+  if (H < 1 || W < 1 || out_ld < W || (ctx->S > 1 && out_slice_stride < static_cast<int64_t>(H) * out_ld))
+    return fail(PTYCHO_E_SHAPE, "strides do not cover %dx%d", H, W);
+  int rc = check_tiles(ctx, tiles, ntiles, H, W);
+  if (rc != PTYCHO_OK) return rc;
+  const size_t span = span_elems(ctx->S, H, W, out_slice_stride, out_ld);
+  PT_BUF(ctx->device, out, span * sizeof(float2), "output");
+  int64_t area = 0;
+  const auto o = range_of(out, span);
+  for (int k = 0; k < ntiles; ++k) {
+    area += static_cast<int64_t>(tiles[k].ty1 - tiles[k].ty0) * (tiles[k].tx1 - tiles[k].tx0);
+    for (int j = 0; j < k; ++j)
+      if (!meet(tile_of(tiles[j]), tile_of(tiles[k])).empty())
+        return fail(PTYCHO_E_SHAPE, "tiles %d and %d overlap", j, k);
+    const auto b = range_of(tiles[k].grad, static_cast<size_t>(ctx->S) * tiles[k].eh * tiles[k].ew);
+    if (o.first < b.second && b.first < o.second) return fail(PTYCHO_E_ARG, "the output shares memory with tile %d", k);
+  }
+  if (area != static_cast<int64_t>(H) * W) return fail(PTYCHO_E_SHAPE, "the tiles do not cover %dx%d", H, W);
+  BoxStage st(ctx);
+  for (int k = 0; k < ntiles && rc == PTYCHO_OK; ++k) {
+    const Rect at = tile_of(tiles[k]);
+    if (at.empty()) continue;
+    float2* p = static_cast<float2*>(out) + static_cast<int64_t>(at.y0) * out_ld + at.x0;
+    rc = st.begin(at, p, out_slice_stride, out_ld, mode == PTYCHO_STITCH_SUM ? ptycho::kBoxZero : ptycho::kBoxCopy);
+    if (mode == PTYCHO_STITCH_INTERIOR) {
+      if (rc == PTYCHO_OK) rc = add_tile(st, tiles[k]);
+    } else {
+      for (int j = 0; j < ntiles && rc == PTYCHO_OK; ++j) rc = add_tile(st, tiles[j]);
+    }
+  }
+  return rc != PTYCHO_OK ? rc : st.flush();
+}
+
+int ptycho_tiles_neighbour_add(ptycho_ctx* ctx, const ptycho_tile_desc* tiles, void* const* dst, int32_t tiles_y,
+                               int32_t tiles_x) {
+  int rc = check_grid(ctx, tiles, tiles_y, tiles_x);
+  if (rc != PTYCHO_OK) return rc;
+  if (!dst) return fail(PTYCHO_E_ARG, "null destinations");
+  std::vector<std::pair<uintptr_t, uintptr_t>> r;
+  const int n = tiles_y * tiles_x;
+  for (int k = 0; k < n; ++k) {
+    const size_t elems = static_cast<size_t>(ctx->S) * tiles[k].eh * tiles[k].ew;
+    if (!dst[k]) return fail(PTYCHO_E_ARG, "null destination %d", k);
+    PT_BUF(ctx->device, dst[k], elems * sizeof(float2), "destination");
+    r.push_back(range_of(tiles[k].grad, elems));
+    r.push_back(range_of(dst[k], elems));
+  }
+  if ((rc = check_disjoint(r)) != PTYCHO_OK) return rc;
+  BoxStage st(ctx);
+  for (int k = 0; k < n && rc == PTYCHO_OK; ++k) {
+    const ptycho_tile_desc& t = tiles[k];
+    const int ty = k / tiles_x, tx = k % tiles_x;
+    rc = st.begin(box_of(t), static_cast<float2*>(dst[k]), static_cast<long long>(t.eh) * t.ew, t.ew, ptycho::kBoxCopy);
+    if (rc == PTYCHO_OK) rc = add_tile(st, t);
+    for (int dy = -1; dy <= 1; ++dy)
+      for (int dx = -1; dx <= 1 && rc == PTYCHO_OK; ++dx)
+        if ((dy != 0 || dx != 0) && ty + dy >= 0 && ty + dy < tiles_y && tx + dx >= 0 && tx + dx < tiles_x)
+          rc = add_tile(st, tiles[(ty + dy) * tiles_x + tx + dx]);
+  }
+  return rc != PTYCHO_OK ? rc : st.flush();
+}
+
+int ptycho_tiles_passes(ptycho_ctx* ctx, const ptycho_tile_desc* tiles, int32_t tiles_y, int32_t tiles_x) {
+  const int rc = check_grid(ctx, tiles, tiles_y, tiles_x);
+  if (rc != PTYCHO_OK) return rc;
+  return enqueue_passes(ctx, std::vector<ptycho_tile_desc>(tiles, tiles + tiles_y * tiles_x), tiles_y, tiles_x);
+}
+
+}  // extern "C"
+
+namespace {
+constexpr int kMaxStateTiles = 65535;  // a grid dimension of the tile kernels
+// The device table of Alg. 1's tiles: object copy, accumulation buffer and batch gradient on each box.
+int tile_states(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int32_t n, std::vector<ptycho::TileDesc>* out) {
+  if (!tiles || n < 1 || n > kMaxStateTiles) return fail(PTYCHO_E_ARG, "tile count %d outside [1, %d]", n, kMaxStateTiles);
+  std::vector<std::pair<uintptr_t, uintptr_t>> r;
+  out->assign(n, ptycho::TileDesc{});
+  for (int k = 0; k < n; ++k) {
+    const ptycho_tile_state& t = tiles[k];
+    if (t.eh < 1 || t.ew < 1 || t.ey0 < 0 || t.ex0 < 0 || t.ty0 < t.ey0 || t.tx0 < t.ex0 || t.ty1 - t.ey0 > t.eh ||
+        t.tx1 - t.ex0 > t.ew || t.ty0 > t.ty1 || t.tx0 > t.tx1)
+      return fail(PTYCHO_E_SHAPE, "tile %d: bad tile or box", k);
+    if (static_cast<int64_t>(t.ew) * ctx->M >= (int64_t(1) << 31))
+      return fail(PTYCHO_E_SHAPE, "tile %d: row stride too large", k);
+    if (!t.obj || !t.acc || !t.grad) return fail(PTYCHO_E_ARG, "tile %d: null buffer", k);
+    const size_t elems = static_cast<size_t>(ctx->S) * t.eh * t.ew;
+    PT_BUF(ctx->device, t.obj, elems * sizeof(float2), "tile object");
+    PT_BUF(ctx->device, t.acc, elems * sizeof(float2), "tile accumulation buffer");
+    PT_BUF(ctx->device, t.grad, elems * sizeof(float2), "tile gradient");
+    for (const void* p : {t.obj, t.acc, t.grad}) r.push_back(range_of(p, elems));
+    ptycho::TileDesc& d = (*out)[k];
+    d.ty0 = t.ty0; d.ty1 = t.ty1; d.tx0 = t.tx0; d.tx1 = t.tx1;
+    d.ey0 = t.ey0; d.ex0 = t.ex0; d.eh = t.eh; d.ew = t.ew;
+    d.grad = static_cast<float2*>(t.grad);
+    d.gslice = static_cast<long long>(t.eh) * t.ew;
+    d.gld = t.ew;
+    d.obj = static_cast<float2*>(t.obj);
+    d.acc = static_cast<float2*>(t.acc);
+  }
+  return check_disjoint(r);
+}
+}  // namespace
+
+extern "C" {
+
+int ptycho_tiles_batch_step(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int32_t ntiles, const int32_t* tile_of_pos,
+                            const void* probe, const int32_t* pos, const float* meas, int32_t total,
+                            const int32_t* index, int32_t n, const int32_t* segments, const int32_t* host_segments,
+                            float step, double* losses) {
+  if (!ctx) return fail(PTYCHO_E_ARG, "null context");
+  if (n < 0 || total < 0 || !std::isfinite(step)) return fail(PTYCHO_E_ARG, "bad count or step");
+  if (!losses || !segments || !host_segments || (n > 0 && (!tile_of_pos || !probe || !pos || !meas || !index)))
+    return fail(PTYCHO_E_ARG, "null pointer argument");
+  if (n > ctx->capacity) return fail(PTYCHO_E_CAPACITY, "%d positions exceed the reserved capacity %d", n, ctx->capacity);
+  std::vector<ptycho::TileDesc> table;
+  int rc = tile_states(ctx, tiles, ntiles, &table);
+  if (rc != PTYCHO_OK) return rc;
+  if (host_segments[0] != 0 || host_segments[ntiles] != n) return fail(PTYCHO_E_ARG, "segments do not span the batch");
+  for (int k = 0; k < ntiles; ++k) {
+    if (host_segments[k + 1] < host_segments[k]) return fail(PTYCHO_E_ARG, "segments decrease at tile %d", k);
+    if (host_segments[k + 1] > host_segments[k] && (tiles[k].eh < ctx->M || tiles[k].ew < ctx->M))
+      return fail(PTYCHO_E_HALO, "tile %d: extended box smaller than a window", k);
+  }
+  rc = check_position_buffers(ctx, nullptr, 0, 0, 0, 0, probe, pos, total, meas);
+  if (rc != PTYCHO_OK) return rc;
+  PT_BUF(ctx->device, tile_of_pos, static_cast<size_t>(total) * sizeof(int32_t), "tile indices");
+  PT_BUF(ctx->device, index, static_cast<size_t>(n) * sizeof(int32_t), "batch positions");
+  PT_BUF(ctx->device, segments, (static_cast<size_t>(ntiles) + 1) * sizeof(int32_t), "segments");
+  PT_BUF(ctx->device, losses, static_cast<size_t>(ntiles) * sizeof(double), "losses");
+  if ((rc = upload_tiles(ctx, table)) != PTYCHO_OK) return rc;
+  if (n > 0) {
+    ptycho::KernelArgs a = base_args(ctx);
+    a.n = n;
+    a.oob_flag = PTYCHO_STATUS_HALO;
+    a.probe = static_cast<const float2*>(probe);
+    a.pos = pos;
+    a.index = index;
+    a.meas = meas;
+    a.tiles = ctx->d_tiles;
+    a.tile_of_pos = tile_of_pos;
+    a.ntiles = ntiles;
+    rc = launch_fused_timed(ctx, a, ptycho::kModeLossGrad);
+    if (rc != PTYCHO_OK) return rc;
+  }
+  PT_HIP(ptycho::launch_tile_step(ctx->d_tiles, ntiles, ctx->S, ctx->M, pos, index, segments, step, ctx->d_loss, losses,
+                                  ctx->stream));
+  return PTYCHO_OK;
+}
+
+int ptycho_tiles_flush(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int32_t tiles_y, int32_t tiles_x, float step) {
+  if (!ctx) return fail(PTYCHO_E_ARG, "null context");
+  if (tiles_y < 1 || tiles_x < 1 || static_cast<int64_t>(tiles_y) * tiles_x > kMaxStateTiles || !std::isfinite(step))
+    return fail(PTYCHO_E_ARG, "bad tile grid or step");
+  const int n = tiles_y * tiles_x;
+  std::vector<ptycho::TileDesc> table;
+  int rc = tile_states(ctx, tiles, n, &table);
+  if (rc != PTYCHO_OK) return rc;
+  std::vector<ptycho_tile_desc> acc(n);
+  for (int k = 0; k < n; ++k) {
+    const ptycho_tile_state& t = tiles[k];
+    acc[k] = {t.ty0, t.ty1, t.tx0, t.tx1, t.ey0, t.ex0, t.eh, t.ew, t.acc};
+  }
+  if ((rc = upload_tiles(ctx, table)) != PTYCHO_OK) return rc;
+  if ((rc = enqueue_passes(ctx, acc, tiles_y, tiles_x)) != PTYCHO_OK) return rc;
+  PT_HIP(ptycho::launch_tile_flush(ctx->d_tiles, n, ctx->S, step, ctx->stream));
+  return PTYCHO_OK;
 }
 
 int ptycho_zero_gradient(ptycho_ctx* ctx, void* grad, int32_t H, int32_t W, int64_t grad_slice_stride,

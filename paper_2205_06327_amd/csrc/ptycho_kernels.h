@@ -31,8 +31,33 @@ struct TileDesc {
   int ey0, ex0, eh, ew;    // extended box
   float2* grad;            // [S][eh][ew] dense
   long long gslice, gld;
+  float2* obj;             // the tile's own object copy (layout of grad), or null: the launch's object
+  float2* acc;             // accumulation buffer of Alg. 1 (layout of grad), or null
 };
 constexpr int kMaxTiles = 4096;
+
+// A list of box operations, passed by value (no upload, so a launch can be captured): dst(y, x) =
+// sum of the sources that hold (y, x), in order.  Coordinates are those of the destination box.
+struct BoxSrc {
+  const float2* p;       // element (s, y, x) at p[s*slice + y*ld + x], y0 <= y < y1, x0 <= x < x1
+  long long slice, ld;
+  int y0, y1, x0, x1;
+};
+constexpr int kBoxZero = 0;  // start from zero
+constexpr int kBoxAdd = 1;   // start from the destination
+constexpr int kBoxCopy = 2;  // start from the first source, which covers the box
+struct BoxOp {
+  float2* dst;
+  long long slice, ld;
+  int h, w, init, nsrc, first;
+};
+struct BoxList {
+  static constexpr int kOps = 16, kSrcs = 64;
+  int nops, nsrcs;
+  BoxOp op[kOps];
+  BoxSrc src[kSrcs];
+};
+static_assert(sizeof(BoxList) <= 3584, "the list travels in the kernel arguments");
 
 struct KernelArgs {
   int M, S, n;
@@ -47,7 +72,8 @@ struct KernelArgs {
   unsigned oob_flag;     // status bit raised for a window outside the box
   const float2* probe;
   long long probe_stride;  // 0: one probe for all positions; else position p uses probe + p*probe_stride
-  const int* pos;        // [n][2] global (y0, x0)
+  const int* pos;        // [..][2] global (y0, x0)
+  const int* index;      // nullable [n]: job p is position index[p] (of pos, meas, tile_of_pos and probes)
   const float2* tw;      // W_M^e, e in [0, M)
   const float2* h;       // separable propagator factor h[k], k in [0, M)
   float* intens;         // forward output [n][M][M]
@@ -119,6 +145,10 @@ hipError_t launch_potential(int mode, float sigma, int S, int H, int W, const fl
                             long long gs, long long gld, float* gv, long long gvs, long long gvld, hipStream_t st);
 hipError_t launch_box_exchange(const float2* src, long long sslice, long long sld, float2* dst, long long dslice,
                                long long dld, int S, int oh, int ow, bool replace, float alpha, hipStream_t st);
+hipError_t launch_box_list(const BoxList& list, int S, int rows, hipStream_t st);
+hipError_t launch_tile_step(const TileDesc* tiles, int ntiles, int S, int M, const int* pos, const int* index,
+                            const int* seg, float step, const double* loss_work, double* losses, hipStream_t st);
+hipError_t launch_tile_flush(const TileDesc* tiles, int ntiles, int S, float step, hipStream_t st);
 hipError_t launch_tile_accumulate(const float2* tile, int S, int eh, int ew, float2* grad, long long gslice,
                                   long long gld, hipStream_t st);
 

@@ -609,12 +609,13 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
   for (int j = 0;; ++j) {
     const int p = job_position(j, a.n, static_cast<int>(gridDim.x), a.run);
     if (p < 0) break;
-    const int gy = a.pos[2 * p], gx = a.pos[2 * p + 1];
+    const int q = a.index != nullptr ? a.index[p] : p;
+    const int gy = a.pos[2 * q], gx = a.pos[2 * q + 1];
     const int y0 = gy - a.oy, x0 = gx - a.ox;
     bool ok;
     jb.win = a.obj + static_cast<long long>(y0) * a.ld + x0;
     if (a.tiles != nullptr) {  // all-tiles mode: the owning tile's box and gradient buffer (uniform)
-      const int tk = a.tile_of_pos[p];
+      const int tk = a.tile_of_pos[q];
       ok = tk >= 0 && tk < a.ntiles;
       unsigned flag = 4u;
       if (ok) {
@@ -629,6 +630,11 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
           jb.grad = T.grad + static_cast<long long>(gy - T.ey0) * T.gld + (gx - T.ex0);
           jb.gld = T.gld;
           jb.gslice = T.gslice;
+          if (T.obj != nullptr) {  // the tile's own object, laid out as its gradient
+            jb.win = T.obj + (jb.grad - T.grad);
+            jb.ld = T.gld;
+            jb.sstride = T.gslice;
+          }
         }
       }
       if (!ok && threadIdx.x == 0) atomicOr(a.status, flag);
@@ -643,8 +649,8 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
       }
       continue;
     }
-    jb.probe = a.probe + static_cast<long long>(p) * a.probe_stride;
-    jb.meas = a.meas + static_cast<long long>(p) * (G::M * G::M);
+    jb.probe = a.probe + static_cast<long long>(q) * a.probe_stride;
+    jb.meas = a.meas + static_cast<long long>(q) * (G::M * G::M);
     jb.intens = a.intens + static_cast<long long>(p) * (G::M * G::M);
     set_columns<G, (MODE == kModeLossGrad || MODE == kModeLossGradProbe)>(jb, L);
     const double f = run_position<G, MODE, G::M == 128, true, true>(jb, sh, twb, hy, ws, L);

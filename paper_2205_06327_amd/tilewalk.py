@@ -212,11 +212,9 @@ class AllTilesWalk:
     def step(self, obj, probe, meas_sorted, grad, loss_per_pos=None):
         """grad <- sum of the embedded tile gradients; returns the total loss (float64 [1]).
         loss_per_pos: optional float64 [n] device tensor receiving f_i in tile order."""
-        B.ptycho_zero_gradient(self.ctx, grad)
         B.ptycho_tiles_grad(self.ctx, obj, self.tiles, self.plan.halo, self.tile_of_pos, probe, self.pos,
                             meas_sorted, loss=self.loss, loss_per_pos=loss_per_pos)
-        for k, p in enumerate(self.plan.plans):
-            B.ptycho_tile_accumulate(self.ctx, self.bufs[k], p.box, grad)
+        B.ptycho_tiles_stitch(self.ctx, self.tiles, grad)
         return self.loss
 
 
@@ -325,11 +323,32 @@ class StreamingTileWalk:
         return self.loss
 
 
+def _dense(ctx: B.Context, plan: TileWalk, bufs) -> bool:
+    """Whether every buffer is a dense array of its tile's extended box in memory of its own, which the
+    whole-grid calls take; other views go box by box."""
+    if len(bufs) != len(plan.plans) or len(bufs) > 4096:
+        return False
+    seen = set()
+    for p, b in zip(plan.plans, bufs):
+        if tuple(b.shape) != (ctx.S, p.box[2], p.box[3]) or not b.is_contiguous():
+            return False
+        seen.add(b.data_ptr())
+    return len(seen) == len(bufs)
+
+
+def _tiles(plan: TileWalk, bufs):
+    return [(p.tile, p.box, b) for p, b in zip(plan.plans, bufs)]
+
+
 def directional_passes(ctx: B.Context, plan: TileWalk, bufs) -> None:
     """Section IV's passes between per-tile buffers (bufs[k] holds tile k's extended box), enqueued
     on the caller's current stream: down every tile column add, up every column replace, along
-    every tile row add, back along every row replace."""
+    every tile row add, back along every row replace.  Dense buffers take one launch per step of a
+    pass."""
     ty_n, tx_n = plan.tiles
+    if _dense(ctx, plan, bufs):
+        B.ptycho_tiles_passes(ctx, _tiles(plan, bufs), plan.tiles)
+        return
 
     def exchange(src: int, dst: int, replace: bool) -> None:
         a, b = plan.plans[src].box, plan.plans[dst].box
@@ -353,8 +372,12 @@ def neighbour_add(ctx: B.Context, plan: TileWalk, src, dst) -> None:
     """Section III's single exchange: dst[k] = src[k] plus, on the overlaps, the original gradients
     src[j] of tile k's (up to) eight direct neighbours; src and dst are separate per-tile buffers on
     the extended boxes.  It sums every contribution to tile k's box only when tiles two apart do
-    not overlap (tile >= 2 halo); the directional passes cover the general case."""
+    not overlap (tile >= 2 halo); the directional passes cover the general case.  Dense buffers take
+    one call that writes every destination once."""
     ty_n, tx_n = plan.tiles
+    if _dense(ctx, plan, src) and _dense(ctx, plan, dst):
+        B.ptycho_tiles_neighbour_add(ctx, _tiles(plan, src), dst, plan.tiles)
+        return
     for k, p in enumerate(plan.plans):
         ty, tx = divmod(k, tx_n)
         origin = (p.box[0], p.box[1])
@@ -369,6 +392,9 @@ def neighbour_add(ctx: B.Context, plan: TileWalk, src, dst) -> None:
 
 def stitch_interiors(ctx: B.Context, plan: TileWalk, bufs, out) -> None:
     """out[:, tile] = interior of bufs[k] for every tile k (Alg. 1's final stitch)."""
+    if _dense(ctx, plan, bufs) and tuple(out.shape[1:]) == (plan.H, plan.W):
+        B.ptycho_tiles_stitch(ctx, _tiles(plan, bufs), out, B.STITCH_INTERIOR)
+        return
     for k, p in enumerate(plan.plans):
         ty0, ty1, tx0, tx1 = p.tile
         ey0, ex0, _, _ = p.box
@@ -488,15 +514,15 @@ class Alg1Walk:
 
     Every tile keeps its own extended copy V_k of the object and an
     accumulation buffer AccBuf_k.  An iteration walks every tile's positions
-    in scan order, ``batch`` at a time: the batch's gradient at V_k
-    (ptycho_tile_grad) is added to AccBuf_k and V_k takes
-    V_k -= step * gradient (ptycho_box_axpy).  After every ``T`` batches and
-    after an iteration's last batch, the directional passes run on the
+    in scan order, ``batch`` at a time: the batch's gradient at V_k is added to
+    AccBuf_k and V_k takes V_k -= step * gradient.  After every ``T`` batches
+    and after an iteration's last batch, the directional passes run on the
     buffers, every tile takes V_k -= step * AccBuf_k, and the buffers are
-    cleared.  With batch = 1 this is the per-probe loop of Alg. 1; a batch of a
-    few hundred positions per tile keeps the GPU busy.  Tiles' launches
-    alternate between two lanes (contexts and streams); the passes and the
-    accumulated update run on the caller's stream after both lanes.
+    cleared.  With batch = 1 this is the per-probe loop of Alg. 1.  The tiles
+    of a batch are independent, so one launch takes all of them
+    (ptycho_tiles_batch_step): a tile's batch alone, often fewer positions
+    than CUs, would leave most of the device idle.  ``lanes`` is accepted for
+    callers that set it; the tiles share their launches whatever its value.
     """
 
     def __init__(self, ctx: B.Context, plan: TileWalk, obj, probe, meas_sorted, step: float, batch: int, T: int,
@@ -505,71 +531,46 @@ class Alg1Walk:
         self.ctx, self.plan = ctx, plan
         self.probe, self.meas = probe, meas_sorted
         self.step_size, self.batch, self.T = float(step), max(1, int(batch)), max(1, int(T))
-        S = ctx.S
-        lanes = max(1, int(lanes))
-        self.ctxs = [ctx] + [B.Context(ctx.M, ctx.S, *ctx.physics, max_positions=self.batch)
-                             for _ in range(lanes - 1)]
-        for c in self.ctxs:
-            c.reserve(self.batch)
-            if c.checkpoint != ctx.checkpoint:
-                c.set_checkpoint(ctx.checkpoint)
-        self.streams = [torch.cuda.Stream(device=device) for _ in range(lanes)]
         self.pos = torch.tensor(plan.pos_sorted, dtype=torch.int32, device=device)
         self.V = []
         for p in plan.plans:
             ey0, ex0, eh, ew = p.box
             self.V.append(obj[:, ey0:ey0 + eh, ex0:ex0 + ew].contiguous())
         self.acc = [torch.zeros_like(v) for v in self.V]
-        eh, ew = plan.max_box
-        self.gbuf = [torch.empty((S, eh, ew), dtype=torch.complex64, device=device) for _ in range(lanes)]
+        self.gbuf = [torch.zeros_like(v) for v in self.V]
         counts = [p.hi - p.lo for p in plan.plans]
         self.steps = max((c + self.batch - 1) // self.batch for c in counts) if counts else 0
         self.losses = torch.zeros((max(self.steps, 1), len(plan.plans)), dtype=torch.float64, device=device)
+        # the positions of step j grouped by tile: index[first[j]:first[j + 1]], tile k's at segments[j, k:k + 2]
+        owner = np.empty(plan.n, dtype=np.int32)
+        index, self._first = [], [0]
+        self._segments = np.zeros((max(self.steps, 1), len(plan.plans) + 1), dtype=np.int32)
+        for k, p in enumerate(plan.plans):
+            owner[p.lo:p.hi] = k
+        for j in range(self.steps):
+            for k, p in enumerate(plan.plans):
+                part = np.arange(min(p.lo + j * self.batch, p.hi), min(p.lo + (j + 1) * self.batch, p.hi))
+                index.append(part)
+                self._segments[j, k + 1] = self._segments[j, k] + len(part)
+            self._first.append(self._first[-1] + int(self._segments[j, -1]))
+        self.tile_of_pos = torch.tensor(owner, dtype=torch.int32, device=device)
+        self.index = torch.tensor(np.concatenate(index) if index else [], dtype=torch.int32, device=device)
+        self.segments = torch.tensor(self._segments, dtype=torch.int32, device=device)
+        ctx.reserve(max(1, int(self._segments[:, -1].max())))
 
     def check(self) -> int:
-        st = 0
-        for c in self.ctxs:
-            st |= c.check()
-        return st
-
-    def _flush(self) -> None:
-        directional_passes(self.ctx, self.plan, self.acc)
-        for k, p in enumerate(self.plan.plans):
-            o = (p.box[0], p.box[1])
-            B.ptycho_box_axpy(self.ctx, -self.step_size, self.acc[k], o, self.V[k], o)
-            B.ptycho_zero_gradient(self.ctx, self.acc[k])
+        return self.ctx.check()
 
     def iteration(self):
         """One pass over every tile's positions; returns the iteration's loss (device float64 [1])."""
-        import torch
-        cur = torch.cuda.current_stream()
-        self.losses.zero_()
-        n_lanes = len(self.ctxs)
+        states = B.tile_states(self.ctx, [(p.tile, p.box, self.V[k], self.acc[k], self.gbuf[k])
+                                          for k, p in enumerate(self.plan.plans)])
         for j in range(self.steps):
-            ev = torch.cuda.Event()
-            ev.record(cur)
-            for s in self.streams:
-                s.wait_event(ev)
-            slot = 0
-            for k, p in enumerate(self.plan.plans):
-                lo = p.lo + j * self.batch
-                hi = min(p.hi, lo + self.batch)
-                if hi <= lo:
-                    continue
-                lane = slot % n_lanes
-                slot += 1
-                ey0, ex0, eh, ew = p.box
-                g = self.gbuf[lane].view(-1)[: self.ctx.S * eh * ew].view(self.ctx.S, eh, ew)
-                with torch.cuda.stream(self.streams[lane]):
-                    B.ptycho_tile_grad(self.ctxs[lane], self.V[k], p.box, p.tile, self.plan.halo, self.plan.H,
-                                       self.plan.W, self.probe, self.pos[lo:hi], self.meas[lo:hi], tile_grad=g,
-                                       loss=self.losses[j, k:k + 1])
-                    B.ptycho_box_axpy(self.ctxs[lane], 1.0, g, (ey0, ex0), self.acc[k], (ey0, ex0))
-                    B.ptycho_box_axpy(self.ctxs[lane], -self.step_size, g, (ey0, ex0), self.V[k], (ey0, ex0))
-            for s in self.streams:
-                cur.wait_stream(s)
+            B.ptycho_tiles_batch_step(self.ctx, states, self.tile_of_pos, self.probe, self.pos, self.meas,
+                                      self.index[self._first[j]:self._first[j + 1]], self.segments[j],
+                                      self._segments[j], self.step_size, self.losses[j])
             if (j + 1) % self.T == 0 or j == self.steps - 1:
-                self._flush()
+                B.ptycho_tiles_flush(self.ctx, states, self.plan.tiles, self.step_size)
         return self.losses.sum().reshape(1)
 
     def stitch(self, out) -> None:
