@@ -102,6 +102,12 @@ __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(
 __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
   return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
+// a * b with the contraction spelled out: which of the two products of a sum is rounded.  Left to the
+// compiler it differs from kernel to kernel, and with it the last bits of the losses; the single-slice
+// gradient kernel names the choice that the multislice kernel compiles to, so that both give the same.
+__device__ __forceinline__ float2 cmul_fma(float2 a, float2 b) {
+  return make_float2(__builtin_fmaf(a.x, b.x, -(a.y * b.y)), __builtin_fmaf(a.x, b.y, a.y * b.x));
+}
 // a * conj(b)
 __device__ __forceinline__ float2 cmulc(float2 a, float2 b) {
   return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);

@@ -38,6 +38,20 @@ __device__ __forceinline__ int opaque_zero() {
 // instructions of 8-byte accesses (measured 2.4 % faster over the whole
 // position-parallel launch).
 typedef float f4v __attribute__((ext_vector_type(4)));
+typedef float f2v __attribute__((ext_vector_type(2)));
+// Accesses through pointers whose address space the compiler loses (they pass
+// through descriptors in memory).  As flat instructions each needs a 64-bit
+// address in registers and counts as an LDS operation, so the exchanges'
+// waits would wait for it.
+template <class T>
+using global_ptr = __attribute__((address_space(1))) T*;
+__device__ __forceinline__ float2 load_global(const float2* row, int i) {
+  const f2v e = ((global_ptr<const f2v>)row)[i];
+  return make_float2(e.x, e.y);
+}
+__device__ __forceinline__ void add_global(float* row, int i, float v) {
+  __builtin_amdgcn_global_atomic_fadd_f32((global_ptr<float>)row + i, v);
+}
 template <int R, int T>
 __device__ __forceinline__ void store_slot(float2* slot, const float2 (&v)[R], int tid) {
   f4v* p = reinterpret_cast<f4v*>(slot) + tid;
@@ -194,7 +208,7 @@ __device__ __forceinline__ void for_window_rows(const float2* __restrict__ base,
   sfor<G::R>([&](auto rc) {
     constexpr int r = decltype(rc)::value;
     const float2* __restrict__ row = base + static_cast<long long>(r * G::Y2 * ldz);
-    f(rc, row[L.x]);
+    f(rc, load_global(row, L.x));
   });
 }
 template <class G>
@@ -220,10 +234,78 @@ __device__ __forceinline__ void scatter_add(float2* __restrict__ gbase, long lon
     constexpr int r = decltype(rc)::value;
     auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(g[r].x), __float_as_uint(g[r].y), false, false);
     float* __restrict__ row = reinterpret_cast<float*>(gbase + static_cast<long long>(r * G::Y2 * gldz));
-    unsafeAtomicAdd(row + off0, __uint_as_float(sw[0]));
-    unsafeAtomicAdd(row + off1, __uint_as_float(sw[1]));
+    add_global(row, off0, __uint_as_float(sw[0]));
+    add_global(row, off1, __uint_as_float(sw[1]));
   });
 }
+
+// Gradient of single-slice positions, summed in registers over a workgroup's
+// run of positions.  Lane x holds the object column whose address is x mod M
+// (set_columns), so from one position to the next in a scan row most lanes keep
+// their pixels and just add; only the lanes whose column left the window (the
+// scan step's worth of M) send theirs to memory.  A position in another row or
+// another gradient buffer sends everything first.  Atomics bound these
+// launches; for a step of 8 of 64 columns this leaves an eighth.  Only one
+// slice: more would not fit the registers (sums_runs has the figures).
+template <class G>
+struct RowSum {
+  float2 acc[G::R];
+  float2* origin = nullptr;     // window origin of the last position (null: nothing held)
+  const float2* buf = nullptr;  // its gradient buffer, row and column
+  int y = 0, x = 0;
+  int ld = 0;                // row pitch of the buffer
+  int lane_x = 0;            // the lane's window column at that position
+
+  // Sends the held values of the window columns that leave (all, or those a step of dx drops) to memory.
+  __device__ __forceinline__ void send(const Lanes<G>& L, bool all, int dx) {
+    const int half = (L.tid >> 5) & 1;
+    const int w0 = (lane_x - 32 * half) & (G::M - 1), w1 = (lane_x - 32 * half + 32) & (G::M - 1);
+    const bool g0 = all || w0 - dx < 0 || w0 - dx >= G::M, g1 = all || w1 - dx < 0 || w1 - dx >= G::M;
+    const bool any0 = __any(g0), any1 = __any(g1);
+    if (!any0 && !any1) return;  // uniform in the wave
+    swap();
+    float2* __restrict__ gbase = origin + static_cast<long long>(L.n2) * ld;
+    auto rows = [&](int off, auto&& value) {
+      const int ldz = ld + opaque_zero();
+      sfor<G::R>([&](auto rc) {
+        constexpr int r = decltype(rc)::value;
+        add_global(reinterpret_cast<float*>(gbase + static_cast<long long>(r * G::Y2 * ldz)), off, value(acc[r]));
+      });
+    };
+    if (g0) rows(2 * w0 + half, [](float2 e) { return e.x; });
+    if (g1) rows(2 * w1 + half, [](float2 e) { return e.y; });
+    swap();
+  }
+  // As in scatter_add: lanes l and l + 32 exchange halves, so that .x holds the first 32 columns' values
+  // of both components and .y the second 32's.  Its own inverse.
+  __device__ __forceinline__ void swap() {
+    sfor<G::R>([&](auto rc) {
+      float2& e = acc[decltype(rc)::value];
+      auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(e.x), __float_as_uint(e.y), false, false);
+      e = make_float2(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    });
+  }
+  __device__ __forceinline__ void add(float2* grad, const float2* base, int gy, int gx, long long pitch,
+                                      const float2 (&g)[G::R], const Lanes<G>& L) {
+    const int dx = gx - x;
+    const bool row = gy == y && base == buf && dx > -G::M && dx < G::M;  // uniform
+    if (origin != nullptr) send(L, !row, dx);
+    const bool keep = origin != nullptr && row && lane_x - dx == L.x;
+    sfor<G::R>([&](auto rc) {
+      constexpr int r = decltype(rc)::value;
+      acc[r] = make_float2((keep ? acc[r].x : 0.0f) + g[r].x, (keep ? acc[r].y : 0.0f) + g[r].y);
+    });
+    origin = grad;
+    buf = base;
+    y = gy;
+    x = gx;
+    ld = static_cast<int>(pitch);
+    lane_x = L.x;
+  }
+  __device__ __forceinline__ void finish(const Lanes<G>& L) {
+    if (origin != nullptr) send(L, true, 0);
+  }
+};
 
 // Adds a gradient window staged in LDS (row-major, row stride RS1, written by
 // e1_write_a) into the complex gradient rows so that every atomic instruction
@@ -263,7 +345,7 @@ __device__ __forceinline__ void scatter_add_lines(float2* __restrict__ gbase, lo
     });
     sfor<JMAX>([&](auto jc) {
       constexpr int j = decltype(jc)::value;
-      if (ok[j]) unsafeAtomicAdd(line0 + 32 * (2 * j + half) + e, val[j]);
+      if (ok[j]) add_global(line0, 32 * (2 * j + half) + e, val[j]);
     });
   }
 }
@@ -309,6 +391,8 @@ struct PositionJob {
   long long gld, gslice;
   float gscale;          // 2 x the upstream gradient factor
   int ck;                // checkpoint interval of the incident waves (1: all kept)
+  const float2* gbuf;    // the gradient buffer and the position in the scan (RowSum)
+  int gy, gx;
   float2* probe_part;    // probe-gradient mode: this workgroup's partial sum (layout A, window columns)
   bool lines;            // 128-windows: stage the gradient and align its atomics row by row (scatter_add_lines)
 };
@@ -326,12 +410,14 @@ struct PositionJob {
 // and two barriers less per slice; without staging or roll the same atomics
 // touch a third more lines (4 % slower than staging).
 // Without a gradient the object's lines decide.
-template <class G, bool GRAD>
+// SUM: by the address mod M instead, whatever the pitch (RowSum).
+template <class G, bool GRAD, bool SUM = false>
 __device__ __forceinline__ void set_columns(PositionJob& jb, Lanes<G>& L) {
   const float2* origin = GRAD ? jb.grad : jb.win;
   const long long ld = GRAD ? jb.gld : jb.ld, slice = GRAD ? jb.gslice : jb.sstride;
   jb.lines = (ld & 15) != 0 || (jb.S > 1 && (slice & 15) != 0);
-  const int roll = jb.lines ? 0 : static_cast<int>((reinterpret_cast<unsigned long long>(origin) >> 3) & 15);
+  const unsigned at = static_cast<unsigned>(reinterpret_cast<unsigned long long>(origin) >> 3);
+  const int roll = SUM ? static_cast<int>(at & (G::M - 1)) : jb.lines ? 0 : static_cast<int>(at & 15);
   L.x = (L.tid - roll) & (G::M - 1);
 }
 
@@ -341,6 +427,7 @@ struct Shared {
   float2 lds[G::LDS_ELEMS];
   float2 hx[G::M];
   double red[G::T / 64];
+  float2 tw[G::M];         // SUM: the pass-B twiddles, read again for each transform
 };
 
 // Loads the separable propagator factor of a reconstruction: the x part into
@@ -366,12 +453,14 @@ __device__ __forceinline__ float2 load_propagator(Shared<G>& sh, const float2* _
 // AHEAD: the adjoint sweep requests each stored incident wave one propagation
 // early (measured faster in the position-parallel launch, no faster in the
 // batched one).
-template <class G, int MODE, bool LINES = false, bool CKPT = false, bool AHEAD = false>
+// SUM: single-slice positions whose gradients are summed in registers.
+template <class G, int MODE, bool LINES = false, bool CKPT = false, bool AHEAD = false, bool SUM = false>
 __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>& sh, const float2 (&twb)[G::X1],
-                                               float2 hy, float2* __restrict__ ws, const Lanes<G>& L) {
+                                               float2 hy, float2* __restrict__ ws, const Lanes<G>& L,
+                                               RowSum<G>* sum = nullptr) {
   constexpr bool GRAD = MODE == kModeLossGrad || MODE == kModeLossGradProbe;
   constexpr bool LOSS = MODE != kModeIntensity;
-  const int S = jb.S;
+  const int S = SUM ? 1 : jb.S;
   // Incident waves for the adjoint sweep.  The slices are cut into segments of
   // ck; the forward sweep keeps the wave entering every segment (a
   // checkpoint, psi_ck, psi_2ck, ...) and every wave of the last segment; the
@@ -397,7 +486,14 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
       store_slot<G::R, G::T>(w, v, L.tid);
     }
     __builtin_amdgcn_sched_barrier(0);
-    sfor<G::R>([&](auto rc) { v[decltype(rc)::value] = cmul(v[decltype(rc)::value], t[decltype(rc)::value]); });
+    sfor<G::R>([&](auto rc) {
+      constexpr int r = decltype(rc)::value;
+      if constexpr (SUM) {
+        v[r] = cmul_fma(v[r], t[r]);
+      } else {
+        v[r] = cmul(v[r], t[r]);
+      }
+    });
     if (s + 1 < S) {
       load_window<G>(t, jb.win + (s + 1) * jb.sstride, jb.ld, L);  // in flight during the propagation
       // after the first slice the buffer was last read by the previous propagation's layout-A reads,
@@ -405,7 +501,9 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
       propagate<G, false>(v, sh.lds, sh.hx, twb, hy, L, s > 0);
     }
   }
-  dft2_a_to_c<G>(v, sh.lds, twb, L, S > 1);
+  float2 tws[G::X1];  // SUM: read from LDS for each transform (RowSum)
+  if constexpr (SUM) load_twb<G>(tws, sh.tw + opaque_zero(), L.m2);
+  dft2_a_to_c<G>(v, sh.lds, SUM ? tws : twb, L, S > 1);
 
   // ---- detector plane, layout C: element (ky, kx = jh*CJ + jl + X1*j2)
   const long long row = static_cast<long long>(L.ky) * G::M;
@@ -437,7 +535,9 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
     const float mod = sqrtf(e.x * e.x + e.y * e.y);
     const float d = mod - a_i;
     acc += static_cast<double>(d) * static_cast<double>(d);
-    const float sc = mod > 0.0f ? jb.gscale * d / mod : 0.0f;
+    // no branch around the division: 32 of them in a row would each wait for the one before
+    const float q = jb.gscale * d / (mod > 0.0f ? mod : 1.0f);
+    const float sc = mod > 0.0f ? q : 0.0f;
     e = make_float2(sc * e.x, sc * e.y);
   });
   // position loss: wave reduction, then across the waves through LDS
@@ -451,7 +551,8 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
     return f;  // the next position's first LDS write is preceded by a barrier
   }
   // ---- adjoint sweep
-  idft2_c_to_a<G>(v, sh.lds, twb, L);  // chi_{S-1} = DFT^H g (its barriers make red[] visible)
+  if constexpr (SUM) load_twb<G>(tws, sh.tw + opaque_zero(), L.m2);
+  idft2_c_to_a<G>(v, sh.lds, SUM ? tws : twb, L);  // chi_{S-1} = DFT^H g (its barriers make red[] visible)
   if (L.tid == 0)
     for (int w = 0; w < G::T / 64; ++w) f += sh.red[w];
   // One adjoint step at slice s of the segment starting at seg, with psi_s
@@ -502,6 +603,10 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
     __builtin_amdgcn_sched_barrier(0);
     bool staged = false;
     if constexpr (LINES) staged = jb.lines;
+    if constexpr (SUM) {
+      sum->add(jb.grad, jb.gbuf, jb.gy, jb.gx, jb.gld, g, L);
+      return;
+    }
     if (staged) {
       // no barrier: the last LDS access before this was the layout-A read that ends every transform,
       // of the slots each thread now writes
@@ -578,7 +683,7 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
 template <int M>
 constexpr int kWavesPerSimd = fused_workgroups_per_cu(M) * Geo<M>::T / 256;
 
-template <int M, int MODE>
+template <int M, int MODE, bool SUM = false>
 __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(KernelArgs a) {
   using G = Geo<M>;
   constexpr bool LOSS = MODE != kModeIntensity;
@@ -587,6 +692,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
   float2 twb[G::X1];
   load_twb<G>(twb, a.tw, L.m2);
   const float2 hy = load_propagator<G>(sh, a.h, L);
+  if constexpr (SUM) load_hx_table<G>(sh.tw, a.tw);
   __syncthreads();
 
   const int S = a.S;
@@ -598,7 +704,8 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
   jb.probe = a.probe;
   jb.gld = a.gld;
   jb.gslice = a.gslice;
-  jb.gscale = 2.0f * (a.grad_scale != nullptr ? static_cast<float>(*a.grad_scale) : 1.0f);
+  const float gscale = 2.0f * (a.grad_scale != nullptr ? static_cast<float>(*a.grad_scale) : 1.0f);
+  jb.gscale = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(gscale)));  // a scalar register
   jb.ck = a.ck;
   jb.probe_part = nullptr;
   if constexpr (MODE == kModeLossGradProbe) {
@@ -606,6 +713,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
     sfor<G::R>([&](auto rc) { jb.probe_part[decltype(rc)::value * G::T + L.tid] = make_float2(0.f, 0.f); });
   }
 
+  RowSum<G> sum;
   for (int j = 0;; ++j) {
     const int p = job_position(j, a.n, static_cast<int>(gridDim.x), a.run);
     if (p < 0) break;
@@ -630,6 +738,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
           jb.grad = T.grad + static_cast<long long>(gy - T.ey0) * T.gld + (gx - T.ex0);
           jb.gld = T.gld;
           jb.gslice = T.gslice;
+          jb.gbuf = T.grad;
           if (T.obj != nullptr) {  // the tile's own object, laid out as its gradient
             jb.win = T.obj + (jb.grad - T.grad);
             jb.ld = T.gld;
@@ -641,6 +750,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
     } else {
       ok = check_window(a, y0, x0, gy, gx);
       jb.grad = a.grad + static_cast<long long>(y0) * a.gld + x0;
+      jb.gbuf = a.grad;
     }
     if (!ok) {
       if (LOSS && threadIdx.x == 0) {
@@ -652,13 +762,16 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
     jb.probe = a.probe + static_cast<long long>(q) * a.probe_stride;
     jb.meas = a.meas + static_cast<long long>(q) * (G::M * G::M);
     jb.intens = a.intens + static_cast<long long>(p) * (G::M * G::M);
-    set_columns<G, (MODE == kModeLossGrad || MODE == kModeLossGradProbe)>(jb, L);
-    const double f = run_position<G, MODE, G::M == 128, true, true>(jb, sh, twb, hy, ws, L);
+    jb.gy = gy;
+    jb.gx = gx;
+    set_columns<G, (MODE == kModeLossGrad || MODE == kModeLossGradProbe), SUM>(jb, L);
+    const double f = run_position<G, MODE, G::M == 128 && !SUM, !SUM, !SUM, SUM>(jb, sh, twb, hy, ws, L, &sum);
     if (LOSS && L.tid == 0) {
       a.loss_work[p] = f;
       if (a.loss_pos != nullptr) a.loss_pos[p] = f;
     }
   }
+  if constexpr (SUM) sum.finish(L);
 }
 
 // ---------------------------------------------------------------------------
@@ -924,6 +1037,11 @@ __global__ void __launch_bounds__(64 * kReduceWaves) probe_reduce_kernel(const f
 // ---------------------------------------------------------------------------
 // launchers (host side)
 // ---------------------------------------------------------------------------
+// Single-slice gradients of 64-windows are summed in registers along a workgroup's run (RowSum): 297 -> 179 us
+// for 9216 positions, 87 -> 63 us for 2550, 24 -> 22 us for 256.  128-windows keep adding each window: their
+// sum (64 VGPRs) left the losses a rounding away from those of every other gradient launch.
+static bool sums_runs(const KernelArgs& a, int mode) { return a.M == 64 && a.S == 1 && mode == kModeLossGrad; }
+
 template <int M, int MODE>
 static hipError_t launch_fused_t(const KernelArgs& a, int grid, hipStream_t st) {
   hipLaunchKernelGGL((fused_kernel<M, MODE>), dim3(grid), dim3(Geo<M>::T), 0, st, a);
@@ -935,7 +1053,14 @@ static hipError_t launch_fused_m(const KernelArgs& a, int mode, int grid, hipStr
   switch (mode) {
     case kModeIntensity: return launch_fused_t<M, kModeIntensity>(a, grid, st);
     case kModeLoss: return launch_fused_t<M, kModeLoss>(a, grid, st);
-    case kModeLossGrad: return launch_fused_t<M, kModeLossGrad>(a, grid, st);
+    case kModeLossGrad:
+      if constexpr (M == 64) {
+        if (sums_runs(a, mode)) {
+          hipLaunchKernelGGL((fused_kernel<M, kModeLossGrad, true>), dim3(grid), dim3(Geo<M>::T), 0, st, a);
+          return hipGetLastError();
+        }
+      }
+      return launch_fused_t<M, kModeLossGrad>(a, grid, st);
     case kModeLossGradProbe: return launch_fused_t<M, kModeLossGradProbe>(a, grid, st);
     default: return hipErrorInvalidValue;
   }
@@ -1002,14 +1127,15 @@ hipError_t launch_shift_probes(const float2* probe, const float* shifts, int n, 
 // runs of 2 did.  Runs of 1 / 2 / 4 / 8 / 16: 4096 eight-slice positions on 1024^2 5.58 / 4.67 / 4.54 / 4.50 /
 // 4.57 ms, two slices 1.52 / 1.35 / 1.26 / 1.22 / 1.25 ms; 16632 16-slice positions on 2048^2 36.4 / 36.2 /
 // 36.5 / 36.9 / 37.8 ms.
-static int launch_run(const KernelArgs& a) {
+static int launch_run(const KernelArgs& a, int mode) {
+  if (sums_runs(a, mode)) return 1 << 20;  // one run per workgroup
   const long long bytes = 2LL * a.S * a.bh * a.bw * static_cast<long long>(sizeof(float2));
   return bytes <= (256LL << 20) ? 8 : 2;
 }
 
 hipError_t launch_fused(const KernelArgs& args, int mode, int grid, hipStream_t st) {
   KernelArgs a = args;
-  a.run = launch_run(a);
+  a.run = launch_run(a, mode);
   if (a.M == 128) return launch_fused_m<128>(a, mode, grid, st);
   if (a.M == 64) return launch_fused_m<64>(a, mode, grid, st);
   return hipErrorInvalidValue;

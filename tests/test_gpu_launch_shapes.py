@@ -95,3 +95,55 @@ def test_runs_of_positions(n):
     L_ref, _, G_ref = oracle.loss_and_gradient(d["obj_eval"], d["probe"], d["pos"], d["meas"], d["H"])
     assert abs(float(loss.item()) - L_ref) <= TOL_L * L_ref
     assert rel_l2(G.cpu().numpy(), G_ref) <= TOL_G
+
+
+@pytest.mark.parametrize("M,n", [(64, 1700), (128, 600)])
+@pytest.mark.parametrize("order", ["serpentine", "walk", "jumps"])
+def test_single_slice_sums_over_a_run(M, n, order):
+    """Single-slice gradients are summed in registers along a workgroup's run of positions: scan rows
+    in both directions, a random walk with steps of 0 to 3 pixels in y and x (rows change within a
+    run, positions repeat), and jumps beyond a window's width within a row; an odd row pitch, and a
+    position outside the object in the middle of a run, which is skipped."""
+    import torch
+    import paper_2205_06327_amd as pt
+    W = 2 * M + 61
+    spec = ps.with_overrides(ps.workload("2d-256-m64" if M == 64 else "2d-1024-m128"), S=1, W=W, ny=2, nx=2, step=4,
+                             noise=False)
+    say(f"single-slice sums M={M} n={n} {order}")
+    rng = np.random.default_rng(3)
+    top = W - M
+    if order == "serpentine":
+        xs = np.arange(0, top + 1, 5)
+        rows = [np.stack([np.full(len(xs), 3 * r % (top + 1)), xs if r % 2 == 0 else xs[::-1]], 1)
+                for r in range(-(-n // len(xs)))]
+        pos = np.concatenate(rows)[:n]
+    elif order == "walk":
+        d = rng.integers(-3, 4, size=(n, 2))
+        d[rng.random(n) < 0.6, 0] = 0
+        pos = np.abs(np.cumsum(d, 0) + top // 2) % (2 * top)
+        pos = np.where(pos > top, 2 * top - pos, pos)
+    else:
+        pos = np.stack([np.repeat(rng.integers(0, top + 1, -(-n // 7)), 7)[:n], rng.integers(0, 2, n) * (M + 30)], 1)
+    pos = np.ascontiguousarray(pos, dtype=np.int32)
+    d = ps.build_inputs(spec)
+    d["H"] = oracle.fresnel_propagator(spec.M, spec.wavelength_A, spec.dz_A, spec.pixel_A)
+    some = rng.permutation(n)[:60]  # patterns of a few positions, repeated: the oracle's cost is in the gradient
+    I = oracle.forward(d["obj_true"], d["probe"], pos[some], d["H"]).astype(np.float32)
+    d["pos"], d["meas"] = pos, I[np.arange(n) % len(some)]
+    t = to_dev(d)
+    ctx = context(spec, n + 1)
+    bad = n // 2
+    dev_pos = torch.cat([t["pos"][:bad], torch.tensor([[top + 1, 0]], dtype=torch.int32, device="cuda:0"), t["pos"][bad:]])
+    dev_meas = torch.cat([t["meas"][:bad], t["meas"][:1], t["meas"][bad:]])
+    loss, G = pt.ptycho_loss_grad(ctx, t["obj"], t["probe"], dev_pos.contiguous(), dev_meas)
+    with pytest.raises(pt.PtychoError) as e:
+        ctx.check()
+    assert e.value.name == "PTYCHO_E_BOUNDS"
+    L_ref, _, G_ref = oracle.loss_and_gradient(d["obj_eval"], d["probe"], d["pos"], d["meas"], d["H"])
+    assert abs(float(loss.item()) - L_ref) <= TOL_L * L_ref
+    assert rel_l2(G.cpu().numpy(), G_ref) <= TOL_G
+    # the same positions through the probe-gradient launch, which adds every window on its own
+    pg = torch.empty_like(t["probe"])
+    loss2, G2 = pt.ptycho_loss_grad(ctx, t["obj"], t["probe"], t["pos"], t["meas"], probe_grad=pg)
+    assert ctx.check() == 0 and float(loss2.item()) == pytest.approx(float(loss.item()), rel=1e-12)
+    assert rel_l2(G2.cpu().numpy(), G.cpu().numpy()) <= 1e-6
