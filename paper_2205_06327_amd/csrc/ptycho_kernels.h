@@ -109,12 +109,12 @@ struct BatchRecon {
 
 struct BatchArgs {
   const BatchRecon* recs;
-  const int* items;      // (reconstruction, position) pairs, grouped by reconstruction
+  const int* items;      // (reconstruction, position) pairs, grouped by reconstruction, in serving order
   int item0, nitems;     // this launch's slice of the list (one window size)
   int smax;              // largest slice count in the slice
   const float2* tw;
   float2* ws;            // grid * ws_slots(smax, 1) * M*M
-  double* item_loss;     // one per item of the whole list
+  double* item_loss;     // one per position of every reconstruction, at its item0 + position
   unsigned* status;
   // Work queues: items [bounds[x], bounds[x+1]) of this launch (relative to
   // item0) are served to the workgroups of XCD x through the counter next[x]

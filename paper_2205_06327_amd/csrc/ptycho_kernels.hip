@@ -814,7 +814,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) batch_kernel(Batc
     if (!(y0 >= 0 && x0 >= 0 && y0 + M <= R.H && x0 + M <= R.W)) {
       if (threadIdx.x == 0) {
         atomicOr(a.status, 1u);
-        a.item_loss[item] = 0.0;
+        a.item_loss[R.item0 + p] = 0.0;
       }
       continue;
     }
@@ -832,7 +832,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) batch_kernel(Batc
     jb.ck = 1;
     set_columns<G, true>(jb, L);
     const double f = run_position<G, kModeLossGrad, G::M == 128>(jb, sh, twb, hy, ws, L);
-    if (L.tid == 0) a.item_loss[item] = f;
+    if (L.tid == 0) a.item_loss[R.item0 + p] = f;
   }
 }
 
@@ -868,25 +868,45 @@ __global__ void __launch_bounds__(256) batch_finalize_kernel(const BatchRecon* _
 }
 
 // mode 0: grad = 0 for every reconstruction; mode 1: obj -= alpha * grad, and
-// the history row counter advances by one.
-__global__ void batch_elementwise_kernel(const BatchRecon* __restrict__ recs, int mode, int* __restrict__ iter) {
+// the history row counter advances by one.  Bound by the bytes (one write, or
+// two reads and a write per value): a wave takes a row, four columns per lane
+// in flight.  One value per thread and step, with two 64-bit divisions to find
+// it, took 249 us for both modes on 32 uneven reconstructions, this 220 us.
+__global__ void __launch_bounds__(256) batch_elementwise_kernel(const BatchRecon* __restrict__ recs, int mode,
+                                                                int* __restrict__ iter) {
+  constexpr int kCols = 4;
   const BatchRecon& R = recs[blockIdx.y];
-  const long long total = static_cast<long long>(R.S) * R.H * R.W;
+  const int rows = R.S * R.H, W = R.W, H = R.H;
   const float al = R.alpha;
-  for (long long i = blockIdx.x * static_cast<long long>(blockDim.x) + threadIdx.x; i < total;
-       i += static_cast<long long>(gridDim.x) * blockDim.x) {
-    const long long s = i / (static_cast<long long>(R.H) * R.W);
-    const long long q = i - s * R.H * R.W;
-    const long long y = q / R.W, x = q - y * R.W;
-    const long long o = s * R.slice_stride + y * R.ld + x;
-    if (mode == 0) {
-      R.grad[o] = make_float2(0.f, 0.f);
-    } else {
-      const float2 g = R.grad[o];
-      float2 t = R.obj[o];
-      t.x -= al * g.x;
-      t.y -= al * g.y;
-      R.obj[o] = t;
+  const long long ld = R.ld, slice = R.slice_stride;
+  const global_ptr<f2v> grad = (global_ptr<f2v>)R.grad;
+  const global_ptr<f2v> obj = (global_ptr<f2v>)R.obj;
+  const int lane = static_cast<int>(threadIdx.x & 63);
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  for (int row = static_cast<int>(blockIdx.x) * 4 + wave; row < rows; row += static_cast<int>(gridDim.x) * 4) {
+    const int s = row / H;
+    const long long o = s * slice + static_cast<long long>(row - s * H) * ld;
+    for (int xb = lane; xb < W; xb += 64 * kCols) {
+      f2v g[kCols], t[kCols];
+      if (mode == 1) {
+        sfor<kCols>([&](auto kc) {
+          constexpr int k = decltype(kc)::value;
+          if (xb + 64 * k < W) {
+            g[k] = grad[o + xb + 64 * k];
+            t[k] = obj[o + xb + 64 * k];
+          }
+        });
+      }
+      sfor<kCols>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        if (xb + 64 * k < W) {
+          if (mode == 0) {
+            grad[o + xb + 64 * k] = f2v{0.f, 0.f};
+          } else {
+            obj[o + xb + 64 * k] = f2v{t[k].x - al * g[k].x, t[k].y - al * g[k].y};
+          }
+        }
+      });
     }
   }
   if (mode == 1 && iter != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *iter += 1;
