@@ -17,9 +17,10 @@ constexpr int kCols = 4;   // columns per lane and step, loaded together
 // Bound: the bytes of the boxes.  The neighbour addition of 16 boxes of 640^2 x
 // 16 slices and the stitch of their interiors took 116 launches and 1.08 ms on
 // the device (each too small to fill it; 1.46 ms with the gaps), as lists 3
-// launches and 0.59 ms (3.5 TB/s); the sum of the 16 boxes into the gradient
+// launches and 0.57 ms (3.6 TB/s); the sum of the 16 boxes into the gradient
 // 0.56 ms as a fill and 16 additions, 0.27 ms as a list.
 __global__ void __launch_bounds__(64 * kWaves) box_list_kernel(BoxList list, int S) {
+  constexpr int kCols = 10;  // 4 / 8 / 10 took 581 / 578 / 570 us for neighbour addition and stitch
   const int o = static_cast<int>(blockIdx.y) / S, s = static_cast<int>(blockIdx.y) % S;
   const BoxOp op = list.op[o];
   const int lane = static_cast<int>(threadIdx.x & 63);

@@ -212,9 +212,16 @@ class AllTilesWalk:
     def step(self, obj, probe, meas_sorted, grad, loss_per_pos=None):
         """grad <- sum of the embedded tile gradients; returns the total loss (float64 [1]).
         loss_per_pos: optional float64 [n] device tensor receiving f_i in tile order."""
+        exact = tuple(grad.shape[1:]) == (self.plan.H, self.plan.W)  # a larger array keeps zeros beyond the tiles
+        if not exact:
+            B.ptycho_zero_gradient(self.ctx, grad)
         B.ptycho_tiles_grad(self.ctx, obj, self.tiles, self.plan.halo, self.tile_of_pos, probe, self.pos,
                             meas_sorted, loss=self.loss, loss_per_pos=loss_per_pos)
-        B.ptycho_tiles_stitch(self.ctx, self.tiles, grad)
+        if exact:
+            B.ptycho_tiles_stitch(self.ctx, self.tiles, grad)
+        else:
+            for k, p in enumerate(self.plan.plans):
+                B.ptycho_tile_accumulate(self.ctx, self.bufs[k], p.box, grad)
         return self.loss
 
 
@@ -330,7 +337,7 @@ def _dense(ctx: B.Context, plan: TileWalk, bufs) -> bool:
         return False
     seen = set()
     for p, b in zip(plan.plans, bufs):
-        if tuple(b.shape) != (ctx.S, p.box[2], p.box[3]) or not b.is_contiguous():
+        if tuple(b.shape) != (ctx.S, p.box[2], p.box[3]) or not b.is_contiguous() or b.numel() == 0:
             return False
         seen.add(b.data_ptr())
     return len(seen) == len(bufs)

@@ -147,3 +147,22 @@ def test_single_slice_sums_over_a_run(M, n, order):
     loss2, G2 = pt.ptycho_loss_grad(ctx, t["obj"], t["probe"], t["pos"], t["meas"], probe_grad=pg)
     assert ctx.check() == 0 and float(loss2.item()) == pytest.approx(float(loss.item()), rel=1e-12)
     assert rel_l2(G2.cpu().numpy(), G.cpu().numpy()) <= 1e-6
+
+
+@pytest.mark.parametrize("M", [64, 128])
+@pytest.mark.parametrize("offset", [0, 1, 2, 3])
+def test_intensities_into_any_float_address(M, offset):
+    """Intensities are stored 16 bytes per lane; the output may start at any float."""
+    import torch
+    import paper_2205_06327_amd as pt
+    spec = ps.with_overrides(ps.workload("2d-256-m64" if M == 64 else "ms8-1024-m128"), S=2, W=M + 20, ny=3, nx=3, step=7,
+                             noise=False)
+    say(f"intensities at float offset {offset}, M={M}")
+    d = problem(spec)
+    t = to_dev(d)
+    n = spec.n
+    buf = torch.full((offset + n * M * M + 5,), -1.0, device="cuda:0")
+    out = buf[offset:offset + n * M * M].view(n, M, M)
+    pt.ptycho_forward(context(spec, n), t["obj"], t["probe"], t["pos"], intens=out)
+    assert rel_l2(out.cpu().numpy(), oracle.forward(d["obj_eval"], d["probe"], d["pos"], d["H"])) <= 1e-5
+    assert bool((buf[:offset] == -1).all()) and bool((buf[offset + n * M * M:] == -1).all())

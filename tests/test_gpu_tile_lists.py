@@ -88,3 +88,34 @@ def test_grid_calls_refuse_bad_tables():
     with pytest.raises(ValueError):
         B.ptycho_tiles_stitch(ctx, [(t, b, v) for (t, b, _), v in zip(tiles, views())], out)  # not dense
     assert float(out.abs().max()) == 0.0
+
+
+def test_single_slice_tiles_of_64_windows():
+    """Single-slice 64-windows are summed in registers along a workgroup's run of positions; in the
+    all-tiles launch a run crosses from one tile's buffer to the next.  Against the undecomposed
+    gradient, also into a gradient array larger than the tiled object (zero beyond it)."""
+    import torch
+    import ptycho_synth as ps
+    from paper_2205_06327_amd.tilewalk import AllTilesWalk
+    from gpu_helpers import context, rel_l2
+    say("single-slice all-tiles launch, M=64")
+    spec = ps.with_overrides(ps.workload("2d-256-m64"), W=256, ny=49, nx=49, step=4)
+    d = ps.build_inputs(spec)
+    obj = torch.tensor(d["obj_eval"], dtype=torch.complex64, device="cuda:0")
+    probe = torch.tensor(d["probe"], dtype=torch.complex64, device="cuda:0")
+    plan = TileWalk(d["pos"], spec.W, spec.W, spec.M, (3, 2), 32)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(2)
+    meas = torch.rand((spec.n, spec.M, spec.M), generator=g, device="cuda:0") * 50
+    ctx = context(spec, spec.n)
+    ref_loss, ref = pt.ptycho_loss_grad(ctx, obj, probe, torch.tensor(plan.pos_sorted, device="cuda:0"), meas)
+    walk = AllTilesWalk(ctx, plan)
+    grad = torch.empty_like(obj)
+    loss = float(walk.step(obj, probe, meas, grad).item())
+    wide = torch.full((1, spec.W + 3, spec.W + 8), 5.0, dtype=torch.complex64, device="cuda:0")
+    walk.step(obj, probe, meas, wide)
+    assert walk.check() == 0
+    assert abs(loss - float(ref_loss.item())) <= 1e-9 * loss
+    assert rel_l2(grad.cpu().numpy(), ref.cpu().numpy()) <= 1e-6
+    assert rel_l2(wide[:, :spec.W, :spec.W].cpu().numpy(), ref.cpu().numpy()) <= 1e-6
+    assert float(wide[:, spec.W:].abs().max()) == 0.0 and float(wide[:, :, spec.W:].abs().max()) == 0.0
