@@ -80,7 +80,10 @@ __device__ __forceinline__ void load_slot(float2 (&v)[R], const float2* slot, in
 // the same gradient lines at the same time, and the memory side's atomics
 // queue (launch_run has the figures).  The remainder of a chunk that no longer
 // fills a round of runs is split evenly, so no block gets more than
-// ceil(chunk / blocks) positions; the blocks with one more are the first ones,
+// ceil(chunk / blocks) positions.  Launches with a block per position cut the
+// positions by the blocks of each XCD instead of evenly: cut evenly, some XCD
+// has a position more than blocks when 8 does not divide the count, and one
+// block took two (100 four-slice positions 239 us, now 138).  The blocks with one more are the first ones,
 // which sit on different CUs (spread over the chunk they shared CUs: 1640
 // eight-slice patterns of 64-windows took 135 us instead of 109).
 __device__ __forceinline__ int job_position(int j, int n, int grid, int run) {
@@ -90,6 +93,10 @@ __device__ __forceinline__ int job_position(int j, int n, int grid, int run) {
     return p < n ? p : -1;
   }
   const int x = b & 7, k = b >> 3;
+  if (n <= grid) {  // one position per block: the blocks of XCD x take as many neighbours as they are
+    const int p = x * (grid >> 3) + (x < (grid & 7) ? x : grid & 7) + k;
+    return j == 0 && p < n ? p : -1;
+  }
   const int gx = (grid - x + 7) >> 3;              // blocks on this XCD
   const int lo = static_cast<int>((static_cast<long long>(x) * n) >> 3);
   const int hi = static_cast<int>((static_cast<long long>(x + 1) * n) >> 3);

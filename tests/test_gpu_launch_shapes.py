@@ -166,3 +166,25 @@ def test_intensities_into_any_float_address(M, offset):
     pt.ptycho_forward(context(spec, n), t["obj"], t["probe"], t["pos"], intens=out)
     assert rel_l2(out.cpu().numpy(), oracle.forward(d["obj_eval"], d["probe"], d["pos"], d["H"])) <= 1e-5
     assert bool((buf[:offset] == -1).all()) and bool((buf[offset + n * M * M:] == -1).all())
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 15, 100, 255])
+def test_a_block_per_position(n):
+    """Every pattern is written once when the launch has a workgroup per position, whatever the count
+    is modulo the 8 XCDs, and again in the order of the positions."""
+    import torch
+    import paper_2205_06327_amd as pt
+    spec = ps.with_overrides(ps.workload("2d-1024-m128"), S=1, W=160, ny=16, nx=16, step=2, noise=False)
+    say(f"a block per position, n={n}")
+    d = ps.build_inputs(spec)
+    pos = np.ascontiguousarray(d["pos"][:n])
+    H = oracle.fresnel_propagator(spec.M, spec.wavelength_A, spec.dz_A, spec.pixel_A)
+    obj = torch.tensor(d["obj_eval"], dtype=torch.complex64, device="cuda:0")
+    probe = torch.tensor(d["probe"], dtype=torch.complex64, device="cuda:0")
+    out = torch.full((n, spec.M, spec.M), -1.0, device="cuda:0")
+    ctx = context(spec, n)
+    pt.ptycho_forward(ctx, obj, probe, torch.tensor(pos, device="cuda:0"), intens=out)
+    assert ctx.check() == 0
+    ref = oracle.forward(d["obj_eval"], d["probe"], pos, H)
+    for i in range(n):
+        assert rel_l2(out[i].cpu().numpy(), ref[i]) <= 1e-5, i
