@@ -468,7 +468,10 @@ int ptycho_tiles_passes(ptycho_ctx* ctx, const ptycho_tile_desc* tiles, int32_t 
  * host.  In order: the gradient of each tile's batch at its V;
  * AccBuf += gradient, V -= step * gradient, gradient = 0; losses[k] (device)
  * = the loss of tile k's batch.  Windows are checked on the device as by
- * ptycho_tiles_grad.  n must not exceed the reserved capacity.
+ * ptycho_tiles_grad; so are the lists: an index outside [0, total) is skipped
+ * and flagged PTYCHO_STATUS_BOUNDS, a position listed under another tile than
+ * its own (tile_of_pos) PTYCHO_STATUS_ASSIGN.  n must not exceed the reserved
+ * capacity.
  *
  * ptycho_tiles_flush: the directional passes on the AccBufs, then
  * V -= step * AccBuf and AccBuf = 0 for every tile.

@@ -1093,8 +1093,9 @@ int tile_states(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int32_t n, std:
   out->assign(n, ptycho::TileDesc{});
   for (int k = 0; k < n; ++k) {
     const ptycho_tile_state& t = tiles[k];
-    if (t.eh < 1 || t.ew < 1 || t.ey0 < 0 || t.ex0 < 0 || t.ty0 < t.ey0 || t.tx0 < t.ex0 || t.ty1 - t.ey0 > t.eh ||
-        t.tx1 - t.ex0 > t.ew || t.ty0 > t.ty1 || t.tx0 > t.tx1)
+    if (t.eh < 1 || t.ew < 1 || t.ey0 < 0 || t.ex0 < 0 || t.ey0 > INT32_MAX - t.eh || t.ex0 > INT32_MAX - t.ew ||
+        t.ty0 < t.ey0 || t.tx0 < t.ex0 || t.ty1 > t.ey0 + t.eh || t.tx1 > t.ex0 + t.ew || t.ty0 > t.ty1 ||
+        t.tx0 > t.tx1)
       return fail(PTYCHO_E_SHAPE, "tile %d: bad tile or box", k);
     if (static_cast<int64_t>(t.ew) * ctx->M >= (int64_t(1) << 31))
       return fail(PTYCHO_E_SHAPE, "tile %d: row stride too large", k);
@@ -1151,6 +1152,8 @@ int ptycho_tiles_batch_step(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int
     a.probe = static_cast<const float2*>(probe);
     a.pos = pos;
     a.index = index;
+    a.total = total;
+    a.seg = segments;
     a.meas = meas;
     a.tiles = ctx->d_tiles;
     a.tile_of_pos = tile_of_pos;
@@ -1158,8 +1161,8 @@ int ptycho_tiles_batch_step(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int
     rc = launch_fused_timed(ctx, a, ptycho::kModeLossGrad);
     if (rc != PTYCHO_OK) return rc;
   }
-  PT_HIP(ptycho::launch_tile_step(ctx->d_tiles, ntiles, ctx->S, ctx->M, pos, index, segments, step, ctx->d_loss, losses,
-                                  ctx->stream));
+  PT_HIP(ptycho::launch_tile_step(ctx->d_tiles, ntiles, ctx->S, ctx->M, pos, tile_of_pos, total, index, n, segments,
+                                  step, ctx->d_loss, losses, ctx->stream));
   return PTYCHO_OK;
 }
 

@@ -73,7 +73,7 @@ struct KernelArgs {
   const float2* probe;
   long long probe_stride;  // 0: one probe for all positions; else position p uses probe + p*probe_stride
   const int* pos;        // [..][2] global (y0, x0)
-  const int* index;      // nullable [n]: job p is position index[p] (of pos, meas, tile_of_pos and probes)
+  const int* index;      // nullable [n], kModeLossGrad: job p is position index[p] (of pos, meas, tile_of_pos)
   const float2* tw;      // W_M^e, e in [0, M)
   const float2* h;       // separable propagator factor h[k], k in [0, M)
   float* intens;         // forward output [n][M][M]
@@ -91,6 +91,8 @@ struct KernelArgs {
   const TileDesc* tiles;
   const int* tile_of_pos;
   int ntiles;
+  int total;             // with index: entries of pos, meas and tile_of_pos; other indices are skipped
+  const int* seg;        // nullable [ntiles + 1], with index and tiles: tile k's jobs are [seg[k], seg[k+1])
 };
 
 // One reconstruction of a batch (device copy of the public descriptor plus
@@ -146,8 +148,9 @@ hipError_t launch_potential(int mode, float sigma, int S, int H, int W, const fl
 hipError_t launch_box_exchange(const float2* src, long long sslice, long long sld, float2* dst, long long dslice,
                                long long dld, int S, int oh, int ow, bool replace, float alpha, hipStream_t st);
 hipError_t launch_box_list(const BoxList& list, int S, int rows, hipStream_t st);
-hipError_t launch_tile_step(const TileDesc* tiles, int ntiles, int S, int M, const int* pos, const int* index,
-                            const int* seg, float step, const double* loss_work, double* losses, hipStream_t st);
+hipError_t launch_tile_step(const TileDesc* tiles, int ntiles, int S, int M, const int* pos, const int* tile_of_pos,
+                            int total, const int* index, int n, const int* seg, float step, const double* loss_work,
+                            double* losses, hipStream_t st);
 hipError_t launch_tile_flush(const TileDesc* tiles, int ntiles, int S, float step, hipStream_t st);
 hipError_t launch_tile_accumulate(const float2* tile, int S, int eh, int ew, float2* grad, long long gslice,
                                   long long gld, hipStream_t st);

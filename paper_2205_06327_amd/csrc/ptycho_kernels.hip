@@ -767,14 +767,26 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
   for (int j = 0;; ++j) {
     const int p = job_position(j, a.n, static_cast<int>(gridDim.x), a.run);
     if (p < 0) break;
-    const int q = a.index != nullptr ? a.index[p] : p;
+    int q = p;
+    if constexpr (MODE == kModeLossGrad) {
+      if (a.index != nullptr) q = a.index[p];  // uniform
+      if (a.index != nullptr && (q < 0 || q >= a.total)) {
+        if (threadIdx.x == 0) {
+          atomicOr(a.status, 1u);
+          a.loss_work[p] = 0.0;
+        }
+        continue;
+      }
+    }
     const int gy = a.pos[2 * q], gx = a.pos[2 * q + 1];
     const int y0 = gy - a.oy, x0 = gx - a.ox;
     bool ok;
     jb.win = a.obj + static_cast<long long>(y0) * a.ld + x0;
-    if (a.tiles != nullptr) {  // all-tiles mode: the owning tile's box and gradient buffer (uniform)
+    if (MODE == kModeLossGrad && a.tiles != nullptr) {  // all-tiles mode: the owning tile's box and gradient buffer (uniform)
       const int tk = a.tile_of_pos[q];
       ok = tk >= 0 && tk < a.ntiles;
+      // listed under the tile that owns it: the update that consumes the gradient goes by the list
+      if (ok && a.seg != nullptr) ok = p >= a.seg[tk] && p < a.seg[tk + 1];
       unsigned flag = 4u;
       if (ok) {
         const TileDesc& T = a.tiles[tk];

@@ -72,10 +72,13 @@ __device__ __forceinline__ int wave_min(int v) {
 // accesses per value of that box; the whole extended boxes in separate passes
 // (zero, two axpy) moved 4 to 5 times as much for 64 positions per tile (31 us
 // per batch of 4 tiles of 576^2 x 8 slices instead of 150).  The
-// first workgroup of a tile also sums its losses, in a fixed order.
+// first workgroup of a tile also sums its losses, in a fixed order.  The lists are device data: an entry
+// that the gradient launch skips (no such position, listed under another tile than its own, outside the
+// box) takes no part here, and a segment is cut to the batch.
 __global__ void __launch_bounds__(64 * kWaves) tile_step_kernel(const TileDesc* __restrict__ tiles, int M,
                                                                const int* __restrict__ pos,
-                                                               const int* __restrict__ index,
+                                                               const int* __restrict__ tile_of_pos, int total,
+                                                               const int* __restrict__ index, int n,
                                                                const int* __restrict__ seg, float step,
                                                                const double* __restrict__ loss_work,
                                                                double* __restrict__ losses) {
@@ -83,7 +86,7 @@ __global__ void __launch_bounds__(64 * kWaves) tile_step_kernel(const TileDesc* 
   __shared__ double part[64 * kWaves];
   const int k = static_cast<int>(blockIdx.y), s = static_cast<int>(blockIdx.z);
   const TileDesc T = tiles[k];
-  const int lo = seg[k], hi = seg[k + 1];
+  const int lo = max(seg[k], 0), hi = min(seg[k + 1], n);
   const int tid = static_cast<int>(threadIdx.x), lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (blockIdx.x == 0 && s == 0) {  // uniform
@@ -101,8 +104,10 @@ __global__ void __launch_bounds__(64 * kWaves) tile_step_kernel(const TileDesc* 
   int y0 = T.eh, x0 = T.ew, ny1 = 0, nx1 = 0;  // box-local corner minima, and minus the maxima
   for (int i = lo + tid; i < hi; i += 64 * kWaves) {
     const int p = index[i];
-    const int y = pos[2 * p] - T.ey0, x = pos[2 * p + 1] - T.ex0;
-    if (y < 0 || x < 0 || y + M > T.eh || x + M > T.ew) continue;  // skipped by the gradient launch too
+    if (p < 0 || p >= total || tile_of_pos[p] != k) continue;  // skipped by the gradient launch too, as the next
+    const int gy = pos[2 * p], gx = pos[2 * p + 1];
+    if (gy < T.ey0 || gx < T.ex0 || gy > T.ey0 + T.eh - M || gx > T.ex0 + T.ew - M) continue;
+    const int y = gy - T.ey0, x = gx - T.ex0;
     y0 = y < y0 ? y : y0;
     x0 = x < x0 ? x : x0;
     ny1 = -(y + M) < ny1 ? -(y + M) : ny1;
@@ -178,10 +183,12 @@ hipError_t launch_box_list(const BoxList& list, int S, int rows, hipStream_t st)
   return hipGetLastError();
 }
 
-hipError_t launch_tile_step(const TileDesc* tiles, int ntiles, int S, int M, const int* pos, const int* index,
-                            const int* seg, float step, const double* loss_work, double* losses, hipStream_t st) {
+hipError_t launch_tile_step(const TileDesc* tiles, int ntiles, int S, int M, const int* pos, const int* tile_of_pos,
+                            int total, const int* index, int n, const int* seg, float step, const double* loss_work,
+                            double* losses, hipStream_t st) {
   hipLaunchKernelGGL(tile_step_kernel, dim3(32, static_cast<unsigned>(ntiles), static_cast<unsigned>(S)),
-                     dim3(64 * kWaves), 0, st, tiles, M, pos, index, seg, step, loss_work, losses);
+                     dim3(64 * kWaves), 0, st, tiles, M, pos, tile_of_pos, total, index, n, seg, step, loss_work,
+                     losses);
   return hipGetLastError();
 }
 
