@@ -91,8 +91,10 @@ struct KernelArgs {
   const TileDesc* tiles;
   const int* tile_of_pos;
   int ntiles;
-  int total;             // with index: entries of pos, meas and tile_of_pos; other indices are skipped
-  const int* seg;        // nullable [ntiles + 1], with index and tiles: tile k's jobs are [seg[k], seg[k+1])
+  // with index (and tiles): entries of pos, meas and tile_of_pos, and the jobs [seg[k], seg[k+1]) of tile k;
+  // other indices, and jobs listed under another tile than their own, are skipped
+  int total;
+  const int* seg;        // [ntiles + 1]
 };
 
 // One reconstruction of a batch (device copy of the public descriptor plus

@@ -733,7 +733,10 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
 template <int M>
 constexpr int kWavesPerSimd = fused_workgroups_per_cu(M) * Geo<M>::T / 256;
 
-template <int M, int MODE, bool SUM = false>
+// LIST: jobs through a list of positions grouped by tile (KernelArgs::index, seg).  Kernels of their own: the
+// checks of the list in the others cost registers that the 128-window gradient does not have (4096
+// single-slice positions 566 -> 600 us).
+template <int M, int MODE, bool SUM = false, bool LIST = false>
 __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(KernelArgs a) {
   using G = Geo<M>;
   constexpr bool LOSS = MODE != kModeIntensity;
@@ -768,9 +771,9 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
     const int p = job_position(j, a.n, static_cast<int>(gridDim.x), a.run);
     if (p < 0) break;
     int q = p;
-    if constexpr (MODE == kModeLossGrad) {
-      if (a.index != nullptr) q = a.index[p];  // uniform
-      if (a.index != nullptr && (q < 0 || q >= a.total)) {
+    if constexpr (LIST) {
+      q = a.index[p];  // uniform
+      if (q < 0 || q >= a.total) {
         if (threadIdx.x == 0) {
           atomicOr(a.status, 1u);
           a.loss_work[p] = 0.0;
@@ -786,7 +789,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
       const int tk = a.tile_of_pos[q];
       ok = tk >= 0 && tk < a.ntiles;
       // listed under the tile that owns it: the update that consumes the gradient goes by the list
-      if (ok && a.seg != nullptr) ok = p >= a.seg[tk] && p < a.seg[tk + 1];
+      if (LIST && ok) ok = p >= a.seg[tk] && p < a.seg[tk + 1];
       unsigned flag = 4u;
       if (ok) {
         const TileDesc& T = a.tiles[tk];
@@ -1124,25 +1127,27 @@ __global__ void __launch_bounds__(64 * kReduceWaves) probe_reduce_kernel(const f
 // sum (64 VGPRs) left the losses a rounding away from those of every other gradient launch.
 static bool sums_runs(const KernelArgs& a, int mode) { return a.M == 64 && a.S == 1 && mode == kModeLossGrad; }
 
-template <int M, int MODE>
+template <int M, int MODE, bool SUM = false, bool LIST = false>
 static hipError_t launch_fused_t(const KernelArgs& a, int grid, hipStream_t st) {
-  hipLaunchKernelGGL((fused_kernel<M, MODE>), dim3(grid), dim3(Geo<M>::T), 0, st, a);
+  hipLaunchKernelGGL((fused_kernel<M, MODE, SUM, LIST>), dim3(grid), dim3(Geo<M>::T), 0, st, a);
   return hipGetLastError();
 }
 
 template <int M>
 static hipError_t launch_fused_m(const KernelArgs& a, int mode, int grid, hipStream_t st) {
+  if (a.index != nullptr && mode != kModeLossGrad) return hipErrorInvalidValue;
   switch (mode) {
     case kModeIntensity: return launch_fused_t<M, kModeIntensity>(a, grid, st);
     case kModeLoss: return launch_fused_t<M, kModeLoss>(a, grid, st);
     case kModeLossGrad:
       if constexpr (M == 64) {
         if (sums_runs(a, mode)) {
-          hipLaunchKernelGGL((fused_kernel<M, kModeLossGrad, true>), dim3(grid), dim3(Geo<M>::T), 0, st, a);
-          return hipGetLastError();
+          return a.index != nullptr ? launch_fused_t<M, kModeLossGrad, true, true>(a, grid, st)
+                                    : launch_fused_t<M, kModeLossGrad, true>(a, grid, st);
         }
       }
-      return launch_fused_t<M, kModeLossGrad>(a, grid, st);
+      return a.index != nullptr ? launch_fused_t<M, kModeLossGrad, false, true>(a, grid, st)
+                                : launch_fused_t<M, kModeLossGrad>(a, grid, st);
     case kModeLossGradProbe: return launch_fused_t<M, kModeLossGradProbe>(a, grid, st);
     default: return hipErrorInvalidValue;
   }
