@@ -430,7 +430,8 @@ int ptycho_box_exchange(ptycho_ctx* ctx, int32_t S, const void* src, int32_t sy0
  * Whole tile grids in one call.  A ptycho_tile_desc names a tile, its extended
  * box and a buffer on it (`grad`, device complex64 [S][eh][ew], dense; S of the
  * context); the buffers must not share memory (E_ARG).  At most 4096 tiles.
- * Sums run in a fixed order.  Stream-ordered; allocate nothing.
+ * Sums run in a fixed order.  Stream-ordered; allocate nothing (Alg. 1's calls
+ * below: up to 4096 tiles).
  *
  * ptycho_tiles_stitch: out (complex64, element (s, y, x) at
  * out[s*out_slice_stride + y*out_ld + x]) from the tiles, which must cover
@@ -472,6 +473,13 @@ int ptycho_tiles_passes(ptycho_ctx* ctx, const ptycho_tile_desc* tiles, int32_t 
  * and flagged PTYCHO_STATUS_BOUNDS, a position listed under another tile than
  * its own (tile_of_pos) PTYCHO_STATUS_ASSIGN.  n must not exceed the reserved
  * capacity.
+ *
+ * The tiles travel in the arguments of the launches, which replace the
+ * context's table of them: nothing depends on an earlier call, so both calls
+ * can be captured without a first run, and a replay does not mind what ran on
+ * the context in between.  They allocate only where the tiles outgrow the
+ * table (more than 4096, then twice as many, ...); outgrown tables live as
+ * long as the context.
  *
  * ptycho_tiles_flush: the directional passes on the AccBufs, then
  * V -= step * AccBuf and AccBuf = 0 for every tile.

@@ -105,7 +105,9 @@ struct ptycho_ctx {
   float2* d_probe_part = nullptr;  // probe-gradient partial sums, grid * M*M
   ptycho::TileDesc* d_tiles = nullptr;  // tile table of ptycho_tiles_grad (kMaxTiles entries)
   std::vector<ptycho::TileDesc> h_tiles;
-  size_t tiles_cap = ptycho::kMaxTiles;
+  ptycho::TileDesc* d_states = nullptr;  // tile table of Alg. 1, written by every call that uses it
+  size_t states_cap = ptycho::kMaxTiles;
+  std::vector<ptycho::TileDesc*> old_states;  // outgrown tables: captured launches may still use them
   float2* d_ws = nullptr;  // incident-wave store, grid * ws_slots(S, ck) * M*M
   int ck = 1;              // checkpoint interval of the incident waves
   double* d_loss = nullptr;  // per-position losses [capacity]
@@ -129,6 +131,8 @@ void free_ctx(ptycho_ctx* c) {
   if (c->d_ws) (void)hipFree(c->d_ws);
   if (c->d_probe_part) (void)hipFree(c->d_probe_part);
   if (c->d_tiles) (void)hipFree(c->d_tiles);
+  if (c->d_states) (void)hipFree(c->d_states);
+  for (ptycho::TileDesc* t : c->old_states) (void)hipFree(t);
   if (c->d_loss) (void)hipFree(c->d_loss);
   if (c->d_status) (void)hipFree(c->d_status);
   delete c;
@@ -275,13 +279,14 @@ int ptycho_create(ptycho_ctx** out, int32_t M, int32_t S, double wavelength_A, d
       (e = hipMalloc(&c->d_status, sizeof(unsigned))) != hipSuccess ||
       (ws_elems > 0 && !c->d_ws && (e = hipMalloc(&c->d_ws, ws_elems * sizeof(float2))) != hipSuccess) ||
       (e = hipMalloc(&c->d_probe_part, static_cast<size_t>(c->grid) * M * M * sizeof(float2))) != hipSuccess ||
-      (e = hipMalloc(&c->d_tiles, ptycho::kMaxTiles * sizeof(ptycho::TileDesc))) != hipSuccess) {
+      (e = hipMalloc(&c->d_tiles, ptycho::kMaxTiles * sizeof(ptycho::TileDesc))) != hipSuccess ||
+      (e = hipMalloc(&c->d_states, ptycho::kMaxTiles * sizeof(ptycho::TileDesc))) != hipSuccess) {
     free_ctx(c);
     return fail(PTYCHO_E_NOMEM, "device allocation failed: %s", hipGetErrorString(e));
   }
   c->bytes = static_cast<int64_t>(2 * M * sizeof(float2) + c->capacity * sizeof(double) + sizeof(unsigned) +
                                   ws_elems * sizeof(float2) + static_cast<size_t>(c->grid) * M * M * sizeof(float2) +
-                                  ptycho::kMaxTiles * sizeof(ptycho::TileDesc));
+                                  2 * ptycho::kMaxTiles * sizeof(ptycho::TileDesc));
   if ((e = hipMemcpy(c->d_tw, tw.data(), M * sizeof(float2), hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMemcpy(c->d_h, h.data(), M * sizeof(float2), hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMemset(c->d_status, 0, sizeof(unsigned))) != hipSuccess || (e = hipDeviceSynchronize()) != hipSuccess) {
@@ -594,30 +599,6 @@ int ptycho_tile_grad(ptycho_ctx* ctx, const void* obj_ext, int32_t ey0, int32_t 
 }  // extern "C"
 
 namespace {
-// The context's device tile table.  It is uploaded only when it changed (a walk passes the same tiles
-// every step).  The copy is stream-ordered after launches that still read the old table, and the host
-// copy it reads is kept unchanged until the stream has passed it.
-int upload_tiles(ptycho_ctx* ctx, std::vector<ptycho::TileDesc>& table) {
-  const bool same = ctx->h_tiles.size() == table.size() &&
-                    std::memcmp(ctx->h_tiles.data(), table.data(), table.size() * sizeof(ptycho::TileDesc)) == 0;
-  if (same) return PTYCHO_OK;
-  PT_HIP(hipStreamSynchronize(ctx->stream));  // the previous upload has been read
-  if (table.size() > ctx->tiles_cap) {  // only Alg. 1 takes more tiles than the context starts with
-    ptycho::TileDesc* d = nullptr;
-    const hipError_t e = hipMalloc(&d, table.size() * sizeof(ptycho::TileDesc));
-    if (e != hipSuccess) return fail(PTYCHO_E_NOMEM, "tile table: %s", hipGetErrorString(e));
-    ctx->h_tiles.clear();
-    PT_HIP(hipFree(ctx->d_tiles));
-    ctx->d_tiles = d;
-    ctx->bytes += static_cast<int64_t>((table.size() - ctx->tiles_cap) * sizeof(ptycho::TileDesc));
-    ctx->tiles_cap = table.size();
-  }
-  ctx->h_tiles.swap(table);
-  PT_HIP(hipMemcpyAsync(ctx->d_tiles, ctx->h_tiles.data(), ctx->h_tiles.size() * sizeof(ptycho::TileDesc),
-                        hipMemcpyHostToDevice, ctx->stream));
-  return PTYCHO_OK;
-}
-
 int tiles_grad_impl(ptycho_ctx* ctx, const void* obj, int32_t H, int32_t W, int64_t slice_stride, int32_t ld,
                     const ptycho_tile_desc* tiles, int32_t ntiles, int32_t halo, const int32_t* tile_of_pos,
                     const void* probe, int64_t probe_stride, const int32_t* pos, int32_t n, const float* meas,
@@ -655,7 +636,17 @@ int tiles_grad_impl(ptycho_ctx* ctx, const void* obj, int32_t H, int32_t W, int6
     d.gslice = static_cast<long long>(t.eh) * t.ew;
     d.gld = t.ew;
   }
-  if ((rc = upload_tiles(ctx, table)) != PTYCHO_OK) return rc;
+  // Upload the table only when it changed (a walk passes the same tiles every step).  The copy is
+  // stream-ordered after launches that still read the old table, and the host copy it reads is
+  // kept unchanged until the stream has passed it.
+  const bool same = ctx->h_tiles.size() == table.size() &&
+                    std::memcmp(ctx->h_tiles.data(), table.data(), table.size() * sizeof(ptycho::TileDesc)) == 0;
+  if (!same) {
+    PT_HIP(hipStreamSynchronize(ctx->stream));  // the previous upload has been read
+    ctx->h_tiles.swap(table);
+    PT_HIP(hipMemcpyAsync(ctx->d_tiles, ctx->h_tiles.data(), ntiles * sizeof(ptycho::TileDesc),
+                          hipMemcpyHostToDevice, ctx->stream));
+  }
   const bool acc = (flags & PTYCHO_ACCUMULATE) != 0;
   if (!acc) PT_HIP(ptycho::launch_zero_tiles(ctx->d_tiles, ntiles, ctx->S, ctx->stream));
   ptycho::KernelArgs a = base_args(ctx);
@@ -1116,6 +1107,24 @@ int tile_states(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int32_t n, std:
   }
   return check_disjoint(r);
 }
+
+// Puts the tiles into the context's device table, in the arguments of launches: nothing is left from an
+// earlier call, so calls can be captured at any time and replayed whatever ran in between, and walks that
+// take turns do not wait for each other.
+int write_states(ptycho_ctx* ctx, const std::vector<ptycho::TileDesc>& table) {
+  if (table.size() > ctx->states_cap) {
+    ptycho::TileDesc* d = nullptr;
+    const size_t cap = std::max(table.size(), 2 * ctx->states_cap);
+    const hipError_t e = hipMalloc(&d, cap * sizeof(ptycho::TileDesc));
+    if (e != hipSuccess) return fail(PTYCHO_E_NOMEM, "tile table: %s", hipGetErrorString(e));
+    ctx->old_states.push_back(ctx->d_states);
+    ctx->d_states = d;
+    ctx->states_cap = cap;
+    ctx->bytes += static_cast<int64_t>(cap * sizeof(ptycho::TileDesc));
+  }
+  PT_HIP(ptycho::launch_set_tiles(table.data(), static_cast<int>(table.size()), ctx->d_states, ctx->stream));
+  return PTYCHO_OK;
+}
 }  // namespace
 
 extern "C" {
@@ -1144,7 +1153,7 @@ int ptycho_tiles_batch_step(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int
   PT_BUF(ctx->device, index, static_cast<size_t>(n) * sizeof(int32_t), "batch positions");
   PT_BUF(ctx->device, segments, (static_cast<size_t>(ntiles) + 1) * sizeof(int32_t), "segments");
   PT_BUF(ctx->device, losses, static_cast<size_t>(ntiles) * sizeof(double), "losses");
-  if ((rc = upload_tiles(ctx, table)) != PTYCHO_OK) return rc;
+  if ((rc = write_states(ctx, table)) != PTYCHO_OK) return rc;
   if (n > 0) {
     ptycho::KernelArgs a = base_args(ctx);
     a.n = n;
@@ -1155,13 +1164,13 @@ int ptycho_tiles_batch_step(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int
     a.total = total;
     a.seg = segments;
     a.meas = meas;
-    a.tiles = ctx->d_tiles;
+    a.tiles = ctx->d_states;
     a.tile_of_pos = tile_of_pos;
     a.ntiles = ntiles;
     rc = launch_fused_timed(ctx, a, ptycho::kModeLossGrad);
     if (rc != PTYCHO_OK) return rc;
   }
-  PT_HIP(ptycho::launch_tile_step(ctx->d_tiles, ntiles, ctx->S, ctx->M, pos, tile_of_pos, total, index, n, segments,
+  PT_HIP(ptycho::launch_tile_step(ctx->d_states, ntiles, ctx->S, ctx->M, pos, tile_of_pos, total, index, n, segments,
                                   step, ctx->d_loss, losses, ctx->stream));
   return PTYCHO_OK;
 }
@@ -1179,9 +1188,9 @@ int ptycho_tiles_flush(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int32_t 
     const ptycho_tile_state& t = tiles[k];
     acc[k] = {t.ty0, t.ty1, t.tx0, t.tx1, t.ey0, t.ex0, t.eh, t.ew, t.acc};
   }
-  if ((rc = upload_tiles(ctx, table)) != PTYCHO_OK) return rc;
+  if ((rc = write_states(ctx, table)) != PTYCHO_OK) return rc;
   if ((rc = enqueue_passes(ctx, acc, tiles_y, tiles_x)) != PTYCHO_OK) return rc;
-  PT_HIP(ptycho::launch_tile_flush(ctx->d_tiles, n, ctx->S, step, ctx->stream));
+  PT_HIP(ptycho::launch_tile_flush(ctx->d_states, n, ctx->S, step, ctx->stream));
   return PTYCHO_OK;
 }
 

@@ -35,6 +35,12 @@ struct TileDesc {
   float2* acc;             // accumulation buffer of Alg. 1 (layout of grad), or null
 };
 constexpr int kMaxTiles = 4096;
+// Tiles of one launch that writes a tile table.
+struct TileChunk {
+  static constexpr int kTiles = 48;
+  TileDesc t[kTiles];
+};
+static_assert(sizeof(TileChunk) <= 3584, "the chunk travels in the kernel arguments");
 
 // A list of box operations, passed by value (no upload, so a launch can be captured): dst(y, x) =
 // sum of the sources that hold (y, x), in order.  Coordinates are those of the destination box.
@@ -150,6 +156,7 @@ hipError_t launch_potential(int mode, float sigma, int S, int H, int W, const fl
 hipError_t launch_box_exchange(const float2* src, long long sslice, long long sld, float2* dst, long long dslice,
                                long long dld, int S, int oh, int ow, bool replace, float alpha, hipStream_t st);
 hipError_t launch_box_list(const BoxList& list, int S, int rows, hipStream_t st);
+hipError_t launch_set_tiles(const TileDesc* host, int ntiles, TileDesc* dev, hipStream_t st);
 hipError_t launch_tile_step(const TileDesc* tiles, int ntiles, int S, int M, const int* pos, const int* tile_of_pos,
                             int total, const int* index, int n, const int* seg, float step, const double* loss_work,
                             double* losses, hipStream_t st);

@@ -58,6 +58,14 @@ __global__ void __launch_bounds__(64 * kWaves) box_list_kernel(BoxList list, int
   }
 }
 
+// Part of a tile table from the kernel arguments to device memory, word by word.
+__global__ void __launch_bounds__(256) set_tiles_kernel(TileChunk chunk, int ntiles, TileDesc* __restrict__ dst) {
+  constexpr int kWords = sizeof(TileDesc) / sizeof(int);
+  const int* src = reinterpret_cast<const int*>(chunk.t);
+  int* out = reinterpret_cast<int*>(dst);
+  for (int i = static_cast<int>(threadIdx.x); i < ntiles * kWords; i += 256) out[i] = src[i];
+}
+
 __device__ __forceinline__ int wave_min(int v) {
   for (int o = 32; o > 0; o >>= 1) {
     const int u = __shfl_xor(v, o);
@@ -181,6 +189,18 @@ hipError_t launch_box_list(const BoxList& list, int S, int rows, hipStream_t st)
   const unsigned gx = static_cast<unsigned>((rows + 2 * kWaves - 1) / (2 * kWaves));
   hipLaunchKernelGGL(box_list_kernel, dim3(gx, static_cast<unsigned>(list.nops * S)), dim3(64 * kWaves), 0, st, list, S);
   return hipGetLastError();
+}
+
+hipError_t launch_set_tiles(const TileDesc* host, int ntiles, TileDesc* dev, hipStream_t st) {
+  for (int k = 0; k < ntiles; k += TileChunk::kTiles) {
+    const int n = ntiles - k < TileChunk::kTiles ? ntiles - k : TileChunk::kTiles;
+    TileChunk c;
+    for (int i = 0; i < n; ++i) c.t[i] = host[k + i];
+    hipLaunchKernelGGL(set_tiles_kernel, dim3(1), dim3(256), 0, st, c, n, dev + k);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_tile_step(const TileDesc* tiles, int ntiles, int S, int M, const int* pos, const int* tile_of_pos,

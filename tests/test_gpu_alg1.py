@@ -88,3 +88,43 @@ def test_batch_step_checks_its_lists(S):
     got = run(lists, lambda seg: seg - (np.arange(5) == 1))
     assert got[0] == "PTYCHO_E_ASSIGN"
     same(got, run([lists[0][:-1]] + lists[1:]))
+
+
+def test_captured_iteration_replays_beside_other_calls():
+    """The first iteration of a walk goes into a graph; between the replays another walk and an all-tiles
+    gradient use the same context.  Every replay is an iteration of the walk, as in eager mode."""
+    import torch
+    from paper_2205_06327_amd.tilewalk import AllTilesWalk, Alg1Walk
+    spec = ps.with_overrides(ps.workload("2d-256-m64"), S=2, W=192, ny=13, nx=13, step=8, tiles=(2, 2), halo=48)
+    say("captured Alg. 1 iteration")
+    d = ps.build_inputs(spec)
+    dev = "cuda:0"
+    obj = torch.tensor(d["obj_eval"], dtype=torch.complex64, device=dev)
+    probe = torch.tensor(d["probe"], dtype=torch.complex64, device=dev)
+    plan = TileWalk(d["pos"], spec.W, spec.W, spec.M, spec.tiles, spec.halo)
+    half = TileWalk(d["pos"][::2], spec.W, spec.W, spec.M, spec.tiles, spec.halo)
+    g = torch.Generator(device=dev)
+    g.manual_seed(8)
+    meas = torch.rand((plan.n, spec.M, spec.M), generator=g, device=dev) * 50
+    ctx = context(spec, plan.n)
+    pt.ptycho_forward(ctx, obj, probe, torch.tensor(plan.pos_sorted, device=dev))
+    eager, walk = (Alg1Walk(ctx, plan, obj.clone(), probe, meas, 1e-7, 16, 2) for _ in range(2))
+    other = Alg1Walk(ctx, half, obj.clone(), probe, meas[:half.n], 1e-7, 8, 1)
+    tiles = AllTilesWalk(ctx, plan)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        loss = walk.iteration()
+    grad, V, W = (torch.empty_like(obj) for _ in range(3))
+    for _ in range(3):
+        other.iteration()
+        tiles.step(obj, probe, meas, grad)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        want = float(eager.iteration().item())
+        assert float(loss.item()) == pytest.approx(want, rel=1e-6)
+        walk.stitch(V)
+        eager.stitch(W)
+        assert rel_l2(V.cpu().numpy(), W.cpu().numpy()) <= 1e-6
+    assert rel_l2(V.cpu().numpy(), obj.cpu().numpy()) > 1e-5  # it moved
+    assert ctx.check() == 0
