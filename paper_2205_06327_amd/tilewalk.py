@@ -542,7 +542,7 @@ class Alg1Walk:
         self.V = []
         for p in plan.plans:
             ey0, ex0, eh, ew = p.box
-            self.V.append(obj[:, ey0:ey0 + eh, ex0:ex0 + ew].contiguous())
+            self.V.append(obj[:, ey0:ey0 + eh, ex0:ex0 + ew].clone(memory_format=torch.contiguous_format))
         self.acc = [torch.zeros_like(v) for v in self.V]
         self.gbuf = [torch.zeros_like(v) for v in self.V]
         counts = [p.hi - p.lo for p in plan.plans]

@@ -1,13 +1,14 @@
-"""Alg. 1's batch step: its lists of positions are device data and checked there."""
+"""Alg. 1 on a grid of tiles: the device's checks of a batch's lists, capture, and the walk against the oracle."""
 import numpy as np
 import pytest
 
+import oracle
 import ptycho_synth as ps
 import paper_2205_06327_amd as pt
 from paper_2205_06327_amd import _binding as B
-from paper_2205_06327_amd.tilewalk import TileWalk
+from paper_2205_06327_amd.tilewalk import Alg1Walk, TileWalk
 
-from gpu_helpers import context, rel_l2, say
+from gpu_helpers import context, problem, rel_l2, say, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -94,7 +95,7 @@ def test_captured_iteration_replays_beside_other_calls():
     """The first iteration of a walk goes into a graph; between the replays another walk and an all-tiles
     gradient use the same context.  Every replay is an iteration of the walk, as in eager mode."""
     import torch
-    from paper_2205_06327_amd.tilewalk import AllTilesWalk, Alg1Walk
+    from paper_2205_06327_amd.tilewalk import AllTilesWalk
     spec = ps.with_overrides(ps.workload("2d-256-m64"), S=2, W=192, ny=13, nx=13, step=8, tiles=(2, 2), halo=48)
     say("captured Alg. 1 iteration")
     d = ps.build_inputs(spec)
@@ -128,3 +129,47 @@ def test_captured_iteration_replays_beside_other_calls():
         assert rel_l2(V.cpu().numpy(), W.cpu().numpy()) <= 1e-6
     assert rel_l2(V.cpu().numpy(), obj.cpu().numpy()) > 1e-5  # it moved
     assert ctx.check() == 0
+
+
+def _walk(spec, d, batch, T, extra=0):
+    import torch
+    t = to_dev(d)
+    plan = TileWalk(d["pos"], spec.W, spec.W, spec.M, spec.tiles, spec.halo)
+    meas = t["meas"][torch.tensor(plan.order, device="cuda:0")]
+    meas = torch.cat([meas, meas[:extra]])
+    alpha = 0.5 * oracle.gd_step_size(d["probe"], d["pos"], spec.W, spec.W, spec.S)
+    return t, alpha, Alg1Walk(context(spec, spec.n), plan, t["obj"], t["probe"], meas, alpha, batch, T)
+
+
+def _matches_oracle(spec, d, t, alpha, walk, batch, T, iterations=2):
+    import torch
+    losses = []
+    for _ in range(iterations):
+        losses.append(float(walk.iteration().item()))
+        assert not any(bool(torch.view_as_real(g).any()) for g in walk.gbuf)  # zero between calls
+    assert walk.check() == 0
+    V = torch.empty_like(t["obj"])
+    walk.stitch(V)
+    ref_l, ref_V = oracle.alg1_tiles(d["obj_eval"], d["probe"], d["pos"], d["meas"], d["H"], spec.tiles, spec.halo,
+                                     alpha, batch, T, iterations)
+    np.testing.assert_allclose(losses, ref_l, rtol=1e-4)
+    # every FP32 write of V_k rounds by up to 2^-24 |V|, |V| ~ 1, against the size of the update
+    V0 = d["obj_eval"].astype(np.complex128)
+    dV = ref_V - V0
+    writes = iterations * (walk.steps + -(-walk.steps // T))
+    tol = 1e-4 + writes * 2.0 ** -24 * np.linalg.norm(V0) / np.linalg.norm(dV)
+    assert rel_l2(V.cpu().numpy() - V0, dV) <= tol
+
+
+@pytest.mark.parametrize("tiles,S", [((3, 1), 1), ((1, 1), 1), ((1, 1), 2), ((3, 1), 2)])
+def test_tiles_keep_their_own_copies(tiles, S):
+    """Tiles of full-width rows: the boxes of a single slice are views of the object that need no copy to be
+    contiguous, and neighbouring ones overlap.  Every V_k is a copy, and the object is not written."""
+    import torch
+    spec = ps.with_overrides(ps.workload("2d-256-m64"), W=192, S=S, ny=13, nx=13, step=8, tiles=tiles, halo=32)
+    say(f"Alg. 1, tiles {tiles}, S={S}")
+    d = problem(spec)
+    t, alpha, walk = _walk(spec, d, 8, 2)
+    before = t["obj"].clone()
+    _matches_oracle(spec, d, t, alpha, walk, 8, 2)
+    assert torch.equal(t["obj"], before)
