@@ -536,7 +536,7 @@ class Alg1Walk:
                  device="cuda:0", lanes: int = 2):
         import torch
         self.ctx, self.plan = ctx, plan
-        self.probe, self.meas = probe, meas_sorted
+        self.probe, self.meas = probe, meas_sorted[:plan.n]
         self.step_size, self.batch, self.T = float(step), max(1, int(batch)), max(1, int(T))
         self.pos = torch.tensor(plan.pos_sorted, dtype=torch.int32, device=device)
         self.V = []

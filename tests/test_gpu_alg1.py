@@ -173,3 +173,12 @@ def test_tiles_keep_their_own_copies(tiles, S):
     before = t["obj"].clone()
     _matches_oracle(spec, d, t, alpha, walk, 8, 2)
     assert torch.equal(t["obj"], before)
+
+
+def test_more_patterns_than_positions():
+    """Patterns beyond the plan's positions are not looked at."""
+    spec = ps.with_overrides(ps.workload("2d-256-m64"), W=192, S=2, ny=9, nx=9, step=8, tiles=(2, 2), halo=48)
+    say("Alg. 1 with more patterns than positions")
+    d = problem(spec)
+    t, alpha, walk = _walk(spec, d, 8, 2, extra=3)
+    _matches_oracle(spec, d, t, alpha, walk, 8, 2)
