@@ -331,16 +331,19 @@ class StreamingTileWalk:
 
 
 def _dense(ctx: B.Context, plan: TileWalk, bufs) -> bool:
-    """Whether every buffer is a dense array of its tile's extended box in memory of its own, which the
-    whole-grid calls take; other views go box by box."""
+    """Whether every buffer is a dense array of its tile's extended box, which the whole-grid calls take;
+    other views go box by box."""
     if len(bufs) != len(plan.plans) or len(bufs) > 4096:
         return False
-    seen = set()
-    for p, b in zip(plan.plans, bufs):
-        if tuple(b.shape) != (ctx.S, p.box[2], p.box[3]) or not b.is_contiguous() or b.numel() == 0:
-            return False
-        seen.add(b.data_ptr())
-    return len(seen) == len(bufs)
+    return all(tuple(b.shape) == (ctx.S, p.box[2], p.box[3]) and b.is_contiguous() and b.numel() > 0
+               for p, b in zip(plan.plans, bufs))
+
+
+def _disjoint(*bufs) -> bool:
+    """Whether no two of the dense buffers share memory, which the whole-grid calls that write tile buffers
+    ask for; box by box only the two buffers of an exchange must not."""
+    spans = sorted((b.data_ptr(), b.data_ptr() + b.numel() * b.element_size()) for b in bufs)
+    return all(a[1] <= b[0] for a, b in zip(spans, spans[1:]))
 
 
 def _tiles(plan: TileWalk, bufs):
@@ -350,10 +353,10 @@ def _tiles(plan: TileWalk, bufs):
 def directional_passes(ctx: B.Context, plan: TileWalk, bufs) -> None:
     """Section IV's passes between per-tile buffers (bufs[k] holds tile k's extended box), enqueued
     on the caller's current stream: down every tile column add, up every column replace, along
-    every tile row add, back along every row replace.  Dense buffers take one launch per step of a
-    pass."""
+    every tile row add, back along every row replace.  Dense buffers in memory of their own take one
+    launch per step of a pass."""
     ty_n, tx_n = plan.tiles
-    if _dense(ctx, plan, bufs):
+    if _dense(ctx, plan, bufs) and _disjoint(*bufs):
         B.ptycho_tiles_passes(ctx, _tiles(plan, bufs), plan.tiles)
         return
 
@@ -379,10 +382,10 @@ def neighbour_add(ctx: B.Context, plan: TileWalk, src, dst) -> None:
     """Section III's single exchange: dst[k] = src[k] plus, on the overlaps, the original gradients
     src[j] of tile k's (up to) eight direct neighbours; src and dst are separate per-tile buffers on
     the extended boxes.  It sums every contribution to tile k's box only when tiles two apart do
-    not overlap (tile >= 2 halo); the directional passes cover the general case.  Dense buffers take
-    one call that writes every destination once."""
+    not overlap (tile >= 2 halo); the directional passes cover the general case.  Dense buffers in
+    memory of their own take one call that writes every destination once."""
     ty_n, tx_n = plan.tiles
-    if _dense(ctx, plan, src) and _dense(ctx, plan, dst):
+    if _dense(ctx, plan, src) and _dense(ctx, plan, dst) and _disjoint(*src, *dst):
         B.ptycho_tiles_neighbour_add(ctx, _tiles(plan, src), dst, plan.tiles)
         return
     for k, p in enumerate(plan.plans):
