@@ -250,17 +250,17 @@ __device__ __forceinline__ void scatter_add(float2* __restrict__ gbase, long lon
 // run of positions.  Lane x holds the object column whose address is x mod M
 // (set_columns), so from one position to the next in a scan row most lanes keep
 // their pixels and just add; only the lanes whose column left the window (the
-// scan step's worth of M) send theirs to memory.  A position in another row or
-// another gradient buffer sends everything first.  Atomics bound these
-// launches; for a step of 8 of 64 columns this leaves an eighth.  Only one
-// slice: more would not fit the registers (sums_runs has the figures).
+// scan step's worth of M) send theirs to memory.  A window that does not start
+// within M values of the last one's (another row, another tile's buffer) or
+// has another row pitch sends everything first; the addresses decide, so buffers
+// may be shared in any way.  Atomics bound these launches; for a step of 8 of 64
+// columns this leaves an eighth.  Only one slice: more would not fit the
+// registers (sums_runs has the figures).
 template <class G>
 struct RowSum {
   float2 acc[G::R];
-  float2* origin = nullptr;     // window origin of the last position (null: nothing held)
-  const float2* buf = nullptr;  // its gradient buffer, row and column
-  int y = 0, x = 0;
-  int ld = 0;                // row pitch of the buffer
+  float2* origin = nullptr;  // window origin of the last position (null: nothing held)
+  int ld = 0;                // its row pitch
   int lane_x = 0;            // the lane's window column at that position
 
   // Sends the held values of the window columns that leave (all, or those a step of dx drops) to memory.
@@ -292,20 +292,17 @@ struct RowSum {
       e = make_float2(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     });
   }
-  __device__ __forceinline__ void add(float2* grad, const float2* base, int gy, int gx, long long pitch,
-                                      const float2 (&g)[G::R], const Lanes<G>& L) {
-    const int dx = gx - x;
-    const bool row = gy == y && base == buf && dx > -G::M && dx < G::M;  // uniform
+  __device__ __forceinline__ void add(float2* grad, long long pitch, const float2 (&g)[G::R], const Lanes<G>& L) {
+    const long long step = origin != nullptr ? grad - origin : G::M;
+    const bool row = static_cast<int>(pitch) == ld && step > -G::M && step < G::M;  // uniform
+    const int dx = row ? static_cast<int>(step) : 0;
     if (origin != nullptr) send(L, !row, dx);
-    const bool keep = origin != nullptr && row && lane_x - dx == L.x;
+    const bool keep = row && lane_x - dx == L.x;
     sfor<G::R>([&](auto rc) {
       constexpr int r = decltype(rc)::value;
       acc[r] = make_float2((keep ? acc[r].x : 0.0f) + g[r].x, (keep ? acc[r].y : 0.0f) + g[r].y);
     });
     origin = grad;
-    buf = base;
-    y = gy;
-    x = gx;
     ld = static_cast<int>(pitch);
     lane_x = L.x;
   }
@@ -435,8 +432,6 @@ struct PositionJob {
   long long gld, gslice;
   float gscale;          // 2 x the upstream gradient factor
   int ck;                // checkpoint interval of the incident waves (1: all kept)
-  const float2* gbuf;    // the gradient buffer and the position in the scan (RowSum)
-  int gy, gx;
   float2* probe_part;    // probe-gradient mode: this workgroup's partial sum (layout A, window columns)
   bool lines;            // 128-windows: stage the gradient and align its atomics row by row (scatter_add_lines)
 };
@@ -654,7 +649,7 @@ __device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>&
     bool staged = false;
     if constexpr (LINES) staged = jb.lines;
     if constexpr (SUM) {
-      sum->add(jb.grad, jb.gbuf, jb.gy, jb.gx, jb.gld, g, L);
+      sum->add(jb.grad, jb.gld, g, L);
       return;
     }
     if (staged) {
@@ -803,7 +798,6 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
           jb.grad = T.grad + static_cast<long long>(gy - T.ey0) * T.gld + (gx - T.ex0);
           jb.gld = T.gld;
           jb.gslice = T.gslice;
-          jb.gbuf = T.grad;
           if (T.obj != nullptr) {  // the tile's own object, laid out as its gradient
             jb.win = T.obj + (jb.grad - T.grad);
             jb.ld = T.gld;
@@ -815,7 +809,6 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
     } else {
       ok = check_window(a, y0, x0, gy, gx);
       jb.grad = a.grad + static_cast<long long>(y0) * a.gld + x0;
-      jb.gbuf = a.grad;
     }
     if (!ok) {
       if (LOSS && threadIdx.x == 0) {
@@ -827,8 +820,6 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
     jb.probe = a.probe + static_cast<long long>(q) * a.probe_stride;
     jb.meas = a.meas + static_cast<long long>(q) * (G::M * G::M);
     jb.intens = a.intens + static_cast<long long>(p) * (G::M * G::M);
-    jb.gy = gy;
-    jb.gx = gx;
     set_columns<G, (MODE == kModeLossGrad || MODE == kModeLossGradProbe), SUM>(jb, L);
     const double f = run_position<G, MODE, G::M == 128 && !SUM, !SUM, !SUM, SUM>(jb, sh, twb, hy, ws, L, &sum);
     if (LOSS && L.tid == 0) {
