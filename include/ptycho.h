@@ -39,7 +39,8 @@
  * pointer beyond the call's stream work.  A context owns its device tables and
  * its workspace (allocated in ptycho_create, ptycho_reserve and
  * ptycho_set_checkpoint only), so the hot calls allocate nothing and are
- * stream-ordered and asynchronous.
+ * stream-ordered and asynchronous.  (Alg. 1 on more than 4096 tiles is the
+ * exception, see ptycho_tiles_batch_step.)
  *
  * Errors: every call returns PTYCHO_OK (0) or a negative code; a call that
  * fails host validation enqueues nothing.  ptycho_last_error() returns a
@@ -98,9 +99,12 @@ enum {
  * (NULL = default stream) on which every later call of this context runs.
  * max_positions bounds n of a single loss/gradient call (the context keeps a
  * per-position loss array of that length); 0 picks a default of 4096.
- * The context also owns the incident-wave store of the adjoint sweep:
- * (#CUs) x (S-1) x M*M complex64 (see ptycho_set_checkpoint), and the
- * probe-gradient partial sums, (#CUs) x M*M complex64.
+ * The context also owns the incident-wave store of the adjoint sweep, G x (S-1)
+ * x M*M complex64 (see ptycho_set_checkpoint), and the probe-gradient partial
+ * sums, G x M*M complex64, for the G workgroups of a gradient launch: one per CU
+ * for 128-windows; for 64-windows three per CU (S = 16: 403 MB on 256 CUs), or
+ * one where max_positions is no more than the CUs or where three cannot be
+ * allocated.
  * Returns PTYCHO_E_UNSUPPORTED for other M or S, PTYCHO_E_NOMEM if the
  * workspace cannot be allocated.
  */
@@ -108,7 +112,8 @@ int ptycho_create(ptycho_ctx** out, int32_t M, int32_t S, double wavelength_A, d
                   double pixel_A, int32_t max_positions, void* stream);
 int ptycho_destroy(ptycho_ctx* ctx);
 int ptycho_set_stream(ptycho_ctx* ctx, void* stream);
-/* Grow the context's per-call position capacity (allocates; not for hot loops). */
+/* Grow the context's per-call position capacity, and the stores for more
+ * workgroups where the capacity now asks for them (allocates; not for hot loops). */
 int ptycho_reserve(ptycho_ctx* ctx, int32_t max_positions);
 /*
  * ptycho_box_axpy: dst += alpha * src on the overlap of two boxes, with the

@@ -98,11 +98,13 @@ struct ptycho_ctx {
   double wavelength = 0, dz = 0, pixel = 0;
   hipStream_t stream = nullptr;
   int device = 0;
-  int grid = 0;            // persistent workgroups of the fused kernels
+  int cus = 0;
+  int grid = 0;            // persistent workgroups of the gradient launches: what the stores below hold
   int capacity = 0;        // positions per call
   float2* d_tw = nullptr;  // W_M^e
   float2* d_h = nullptr;   // separable propagator factor
-  float2* d_probe_part = nullptr;  // probe-gradient partial sums, grid * M*M
+  float2* d_probe_part = nullptr;  // probe-gradient partial sums, parts * M*M
+  int parts = 0;                   // at least grid
   ptycho::TileDesc* d_tiles = nullptr;  // tile table of ptycho_tiles_grad (kMaxTiles entries)
   std::vector<ptycho::TileDesc> h_tiles;
   ptycho::TileDesc* d_states = nullptr;  // tile table of Alg. 1, written by every call that uses it
@@ -110,6 +112,7 @@ struct ptycho_ctx {
   std::vector<ptycho::TileDesc*> old_states;  // outgrown tables: captured launches may still use them
   float2* d_ws = nullptr;  // incident-wave store, grid * ws_slots(S, ck) * M*M
   int ck = 1;              // checkpoint interval of the incident waves
+  int64_t store_bytes = 0;  // of d_ws and d_probe_part
   double* d_loss = nullptr;  // per-position losses [capacity]
   unsigned* d_status = nullptr;
   int64_t bytes = 0;
@@ -136,6 +139,49 @@ void free_ctx(ptycho_ctx* c) {
   if (c->d_loss) (void)hipFree(c->d_loss);
   if (c->d_status) (void)hipFree(c->d_status);
   delete c;
+}
+
+// Persistent workgroups of a launch: as many as the device holds at once (fused_workgroups_per_cu).  One
+// 64-window workgroup per CU left each SIMD a single wave and nothing to issue while it waited: 1107
+// two-slice positions (a pass with its shifted probes) took 170 us with 256 workgroups and 144 us with 768,
+// 1640 eight-slice patterns 235 and 111 us.
+int most_workgroups(const ptycho_ctx* c) { return c->cus * ptycho::fused_workgroups_per_cu(c->M); }
+
+// Stores of the gradient launches (incident waves, probe partials) for `grid` workgroups at checkpoint
+// interval ck; the old ones stay until the new ones are there.
+hipError_t set_stores(ptycho_ctx* c, int grid, int ck) {
+  const size_t slot = static_cast<size_t>(c->M) * c->M * sizeof(float2);
+  const size_t ws_bytes = static_cast<size_t>(grid) * ptycho::ws_slots(c->S, ck) * slot;
+  const int parts = std::max(grid, c->parts);
+  float2 *ws = nullptr, *part = nullptr;
+  hipError_t e = ws_bytes > 0 ? hipMalloc(&ws, ws_bytes) : hipSuccess;
+  if (e == hipSuccess && parts > c->parts) e = hipMalloc(&part, parts * slot);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    if (ws) (void)hipFree(ws);
+    return e;
+  }
+  if (c->d_ws) (void)hipFree(c->d_ws);
+  c->d_ws = ws;
+  if (part) {
+    if (c->d_probe_part) (void)hipFree(c->d_probe_part);
+    c->d_probe_part = part;
+    c->parts = parts;
+  }
+  c->grid = grid;
+  c->ck = ck;
+  const int64_t bytes = static_cast<int64_t>(ws_bytes + parts * slot);
+  c->bytes += bytes - c->store_bytes;
+  c->store_bytes = bytes;
+  return hipSuccess;
+}
+
+// The same for as many workgroups as gradient launches of the context's capacity can use, or one per CU if
+// there is no room for more.
+hipError_t fit_stores(ptycho_ctx* c, int ck) {
+  const int most = most_workgroups(c);
+  if (most > c->cus && c->capacity > c->cus && set_stores(c, most, ck) == hipSuccess) return hipSuccess;
+  return set_stores(c, c->cus, ck);
 }
 
 int validate_windows_host(const int32_t* pos, int32_t n, int32_t H, int32_t W, int32_t M) {
@@ -189,7 +235,8 @@ ptycho::KernelArgs base_args(const ptycho_ctx* c) {
 
 // Launch of a fused kernel, bracketed by timing events when profiling.
 int launch_fused_timed(ptycho_ctx* c, const ptycho::KernelArgs& a, int mode) {
-  const int grid = a.n < c->grid ? a.n : c->grid;
+  const bool stores = mode == ptycho::kModeLossGrad || mode == ptycho::kModeLossGradProbe;
+  const int grid = std::min(a.n, stores ? c->grid : most_workgroups(c));
   const bool timed = c->profiling && c->ev_used < c->ev_n.size();
   if (c->profiling && !timed) ++c->dropped;
   if (timed) PT_HIP(hipEventRecord(c->ev[2 * c->ev_used], c->stream));
@@ -248,12 +295,7 @@ int ptycho_create(ptycho_ctx** out, int32_t M, int32_t S, double wavelength_A, d
     free_ctx(c);
     return hip_fail(e, "device query");
   }
-  // Persistent workgroups: as many as the device holds at once (fused_workgroups_per_cu).  One 64-window
-  // workgroup per CU left each SIMD a single wave and nothing to issue while it waited: 1107 two-slice
-  // positions (a pass with its shifted probes) took 170 us with 256 workgroups and 144 us with 768, 1640
-  // eight-slice patterns 235 and 111 us.
-  const int per_cu = ptycho::fused_workgroups_per_cu(M);
-  c->grid = (cus > 0 ? cus : 256) * per_cu;
+  c->cus = cus > 0 ? cus : 256;
   c->capacity = max_positions > 0 ? max_positions : 4096;
 
   // Tables computed in double precision, rounded once to float.
@@ -265,28 +307,19 @@ int ptycho_create(ptycho_ctx** out, int32_t M, int32_t S, double wavelength_A, d
     const double ph = -kPi * wavelength_A * dz_A * f * f;
     h[e2] = make_float2(static_cast<float>(std::cos(ph)), static_cast<float>(std::sin(ph)));
   }
-  size_t ws_elems = static_cast<size_t>(c->grid) * ptycho::ws_slots(S, 1) * M * M;
-  if (per_cu > 1 && ws_elems > 0 && hipMalloc(&c->d_ws, ws_elems * sizeof(float2)) != hipSuccess) {
-    // no room for the larger store: one workgroup per CU
-    (void)hipGetLastError();
-    c->d_ws = nullptr;
-    c->grid /= per_cu;
-    ws_elems /= per_cu;
-  }
+  // the tables before the stores: what is left decides how many workgroups those can be for
   if ((e = hipMalloc(&c->d_tw, M * sizeof(float2))) != hipSuccess ||
       (e = hipMalloc(&c->d_h, M * sizeof(float2))) != hipSuccess ||
       (e = hipMalloc(&c->d_loss, static_cast<size_t>(c->capacity) * sizeof(double))) != hipSuccess ||
       (e = hipMalloc(&c->d_status, sizeof(unsigned))) != hipSuccess ||
-      (ws_elems > 0 && !c->d_ws && (e = hipMalloc(&c->d_ws, ws_elems * sizeof(float2))) != hipSuccess) ||
-      (e = hipMalloc(&c->d_probe_part, static_cast<size_t>(c->grid) * M * M * sizeof(float2))) != hipSuccess ||
       (e = hipMalloc(&c->d_tiles, ptycho::kMaxTiles * sizeof(ptycho::TileDesc))) != hipSuccess ||
-      (e = hipMalloc(&c->d_states, ptycho::kMaxTiles * sizeof(ptycho::TileDesc))) != hipSuccess) {
+      (e = hipMalloc(&c->d_states, ptycho::kMaxTiles * sizeof(ptycho::TileDesc))) != hipSuccess ||
+      (e = fit_stores(c, 1)) != hipSuccess) {
     free_ctx(c);
     return fail(PTYCHO_E_NOMEM, "device allocation failed: %s", hipGetErrorString(e));
   }
-  c->bytes = static_cast<int64_t>(2 * M * sizeof(float2) + c->capacity * sizeof(double) + sizeof(unsigned) +
-                                  ws_elems * sizeof(float2) + static_cast<size_t>(c->grid) * M * M * sizeof(float2) +
-                                  2 * ptycho::kMaxTiles * sizeof(ptycho::TileDesc));
+  c->bytes += static_cast<int64_t>(2 * M * sizeof(float2) + c->capacity * sizeof(double) + sizeof(unsigned) +
+                                   2 * ptycho::kMaxTiles * sizeof(ptycho::TileDesc));
   if ((e = hipMemcpy(c->d_tw, tw.data(), M * sizeof(float2), hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMemcpy(c->d_h, h.data(), M * sizeof(float2), hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMemset(c->d_status, 0, sizeof(unsigned))) != hipSuccess || (e = hipDeviceSynchronize()) != hipSuccess) {
@@ -321,6 +354,8 @@ int ptycho_reserve(ptycho_ctx* ctx, int32_t max_positions) {
   ctx->d_loss = p;
   ctx->bytes += static_cast<int64_t>(max_positions - ctx->capacity) * static_cast<int64_t>(sizeof(double));
   ctx->capacity = max_positions;
+  if (ctx->grid < most_workgroups(ctx) && ctx->capacity > ctx->cus)
+    (void)set_stores(ctx, most_workgroups(ctx), ctx->ck);  // without the room for them the present ones do
   return PTYCHO_OK;
 }
 
@@ -778,25 +813,13 @@ int ptycho_set_checkpoint(ptycho_ctx* ctx, int32_t interval) {
   if (!ctx) return fail(PTYCHO_E_ARG, "null context");
   if (interval < 1 || interval > 64) return fail(PTYCHO_E_ARG, "checkpoint interval %d outside [1, 64]", interval);
   if (interval == ctx->ck) return PTYCHO_OK;
-  const size_t old_elems = static_cast<size_t>(ctx->grid) * ptycho::ws_slots(ctx->S, ctx->ck) * ctx->M * ctx->M;
-  const size_t new_elems = static_cast<size_t>(ctx->grid) * ptycho::ws_slots(ctx->S, interval) * ctx->M * ctx->M;
-  if (new_elems != old_elems) {
-    PT_HIP(hipStreamSynchronize(ctx->stream));  // launches in flight may still use the store
-    float2* ws = nullptr;
-    if (new_elems > 0) {
-      hipError_t e = hipMalloc(&ws, new_elems * sizeof(float2));
-      if (e != hipSuccess) return fail(PTYCHO_E_NOMEM, "wave store: %s", hipGetErrorString(e));
-    }
-    float2* old = ctx->d_ws;
-    ctx->d_ws = ws;
-    ctx->bytes += static_cast<int64_t>(new_elems) * static_cast<int64_t>(sizeof(float2)) -
-                  static_cast<int64_t>(old_elems) * static_cast<int64_t>(sizeof(float2));
+  if (ptycho::ws_slots(ctx->S, interval) == ptycho::ws_slots(ctx->S, ctx->ck)) {
     ctx->ck = interval;
-    if (old) PT_HIP(hipFree(old));  // the context already uses the new store
     return PTYCHO_OK;
   }
-  ctx->ck = interval;
-  return PTYCHO_OK;
+  PT_HIP(hipStreamSynchronize(ctx->stream));  // launches in flight may still use the store
+  const hipError_t e = fit_stores(ctx, interval);
+  return e == hipSuccess ? PTYCHO_OK : fail(PTYCHO_E_NOMEM, "wave store: %s", hipGetErrorString(e));
 }
 
 namespace {

@@ -64,3 +64,83 @@ done(r=r, before=before, after=R.host_hip_used())
     assert [x for _, x, _ in out["r"]] == [[], ["malloc"], [], [], []]
     assert [n for _, _, n in out["r"]] == [2 * -(-k // 48) for k in (4096, 4160, 4900, 8190, 4160)]
     assert out["before"] > 0 and out["after"] == 0
+
+
+def test_stores_fit_the_capacity():
+    """64-window contexts hold stores for three workgroups per CU, 128-windows for one; a context whose gradient
+    calls cannot use more than one per CU holds no more, until reserve raises the capacity.  Pattern launches,
+    which need no store, take the whole device either way."""
+    out = host_hip.run(r'''
+def forward(h, M, n):
+    log()
+    rc = L.ptycho_forward(h, device(1 << 20), 256, 256, c_int64(1 << 16), 256, device(1 << 17), device(1 << 20), n,
+                          device(4 * n * M * M))
+    return rc, log()
+def grad(h, M, n, probe_grad):
+    log()
+    d = [device(1 << 20) for _ in range(8)]
+    rc = L.ptycho_loss_grad_probe(h, d[0], 256, 256, c_int64(1 << 16), 256, d[1], d[2], n, d[3], d[4], None, d[5],
+                                  c_int64(1 << 16), 256, d[6] if probe_grad else None, 0, None)
+    return rc, [x for x in log() if "fused_kernel" in x]
+r = {}
+for name, M, capacity in (("one", 64, 1), ("cus", 64, 256), ("more", 64, 257), ("large", 128, 5000)):
+    rc, h = context(M, 5, capacity)
+    r[name] = [rc, L.ptycho_workspace_bytes(h), forward(h, M, 5000), grad(h, M, min(capacity, 5000), True)]
+    assert L.ptycho_workspace_bytes(h) == R.host_hip_used()
+    if name == "one":
+        r["reserve"] = [L.ptycho_reserve(h, 5000), L.ptycho_workspace_bytes(h), grad(h, M, 5000, False)]
+        r["interval"] = [L.ptycho_set_checkpoint(h, 2), L.ptycho_workspace_bytes(h), grad(h, M, 5000, False)]
+        assert L.ptycho_workspace_bytes(h) == R.host_hip_used()
+    L.ptycho_destroy(h)
+    assert R.host_hip_used() == 0
+done(**r)
+''')
+    slot = 64 * 64 * 8
+    tables = out["one"][1] - 256 * 5 * slot
+    assert 0 < tables < 1 << 20
+    assert out["cus"][1] == 256 * 5 * slot + tables + 8 * 255
+    assert out["more"][1] == 768 * 5 * slot + tables + 8 * 256
+    assert out["large"][1] == 256 * 5 * 4 * slot + tables + 8 * 4999 + 2 * 8 * 64
+    for name, wide, launched in (("one", 768, 1), ("cus", 768, 256), ("more", 768, 257), ("large", 256, 256)):
+        rc, _, (rc_f, forward), (rc_g, grad) = out[name]
+        assert rc == rc_f == rc_g == 0
+        assert f" grid {wide} 1 1 " in forward[0] and f" grid {launched} 1 1 " in grad[0]
+    rc, total, (rc_g, grad) = out["reserve"]
+    assert rc == rc_g == 0 and " grid 768 1 1 " in grad[0]
+    assert total == 768 * 5 * slot + tables + 8 * 4999
+    rc, total, (rc_g, grad) = out["interval"]  # S = 5, interval 2: two checkpoints, an inner and the parked wave
+    assert rc == rc_g == 0 and " grid 768 1 1 " in grad[0]
+    assert total == 768 * (4 + 1) * slot + tables + 8 * 4999
+
+
+def test_contexts_fit_where_one_workgroup_per_cu_fits():
+    """Whatever the room, a context comes up where the stores of one workgroup per CU fit, and changes its
+    checkpoint interval where the new store fits beside the old one; a refusal leaves it as it was."""
+    out = host_hip.run(r'''
+slot = 64 * 64 * 8
+rc, h = context(64, 9, 300)
+full = L.ptycho_workspace_bytes(h)
+L.ptycho_destroy(h)
+small = full - 512 * 9 * slot
+r = []
+for k in range(0, 21):
+    room = small + (full - small) * k // 20 + (k // 20) * 4096 - (0 if k else 1)
+    budget(room)
+    rc, h = context(64, 9, 300)
+    r.append([rc, L.ptycho_workspace_bytes(h) if rc == 0 else R.host_hip_used()])
+    if rc == 0: L.ptycho_destroy(h)
+    assert R.host_hip_used() == 0
+budget(full)
+_, h = context(64, 9, 300)
+assert L.ptycho_set_checkpoint(h, 3) == -8 and L.ptycho_workspace_bytes(h) == full  # no room beside the old one
+budget(full + 256 * 5 * slot)
+c = [L.ptycho_set_checkpoint(h, 3), L.ptycho_workspace_bytes(h), R.host_hip_used()]
+done(r=r, full=full, small=small, c=c)
+''')
+    assert out["r"][0] == [-8, 0]
+    assert all(rc == 0 for rc, _ in out["r"][1:])
+    assert all(b == out["small"] for _, b in out["r"][1:20]) and out["r"][20][1] == out["full"]
+    # interval 3 for one workgroup per CU: two checkpoints, two inner waves and the parked one; the probe
+    # partials stay
+    after = out["full"] - (768 * 8 - 256 * 5) * 32768
+    assert out["c"] == [0, after, after]
