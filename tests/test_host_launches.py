@@ -144,3 +144,31 @@ done(r=r, full=full, small=small, c=c)
     # partials stay
     after = out["full"] - (768 * 8 - 256 * 5) * 32768
     assert out["c"] == [0, after, after]
+
+
+def test_a_stitch_of_many_tiles_costs_the_host_no_more_than_the_boxes():
+    """4096 tiles, as a grid and as strips: finding the boxes over each tile takes the host no longer than
+    twice the calls that add box by box (all pairs of tiles took eight times as long)."""
+    out = host_hip.run(r'''
+import time
+r = []
+for H, W, ny, nx, halo in ((4096, 4096, 64, 64, 32), (64, 65536, 1, 4096, 8), (65536, 64, 4096, 1, 8)):
+    rc, h = context(64, 1, 16)
+    bx = list(boxes(H, W, ny, nx, halo))
+    tiles = (Tile * len(bx))(*[Tile(*b, device(b[6] * b[7] * 8)) for b in bx])
+    dst = device(H * W * 8)
+    best = [1e9, 1e9]
+    for _ in range(3):
+        t = time.perf_counter()
+        rc |= L.ptycho_tiles_stitch(h, tiles, len(bx), H, W, dst, c_int64(H * W), W, 0)
+        best[0] = min(best[0], time.perf_counter() - t)
+        t = time.perf_counter()
+        for b, k in zip(bx, tiles):
+            rc |= L.ptycho_tile_accumulate(h, c_void_p(k.grad), b[4], b[5], b[6], b[7], H, W, dst, c_int64(H * W), W)
+        best[1] = min(best[1], time.perf_counter() - t)
+        R.host_hip_clear()
+    r.append([rc] + best)
+done(r=r)
+''')
+    for rc, stitch, by_box in out["r"]:
+        assert rc == 0 and stitch <= 2 * by_box, out
