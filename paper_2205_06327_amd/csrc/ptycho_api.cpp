@@ -234,13 +234,13 @@ ptycho::KernelArgs base_args(const ptycho_ctx* c) {
 }
 
 // Launch of a fused kernel, bracketed by timing events when profiling.
-int launch_fused_timed(ptycho_ctx* c, const ptycho::KernelArgs& a, int mode) {
+int launch_fused_timed(ptycho_ctx* c, const ptycho::KernelArgs& a, int mode, int64_t tile_bytes = 0) {
   const bool stores = mode == ptycho::kModeLossGrad || mode == ptycho::kModeLossGradProbe;
   const int grid = std::min(a.n, stores ? c->grid : most_workgroups(c));
   const bool timed = c->profiling && c->ev_used < c->ev_n.size();
   if (c->profiling && !timed) ++c->dropped;
   if (timed) PT_HIP(hipEventRecord(c->ev[2 * c->ev_used], c->stream));
-  PT_HIP(ptycho::launch_fused(a, mode, grid, c->stream));
+  PT_HIP(ptycho::launch_fused(a, mode, grid, c->stream, tile_bytes));
   if (timed) {
     PT_HIP(hipEventRecord(c->ev[2 * c->ev_used + 1], c->stream));
     c->ev_n[c->ev_used++] = a.n;
@@ -653,6 +653,7 @@ int tiles_grad_impl(ptycho_ctx* ctx, const void* obj, int32_t H, int32_t W, int6
   PT_BUF(ctx->device, loss, sizeof(double), "loss");
   PT_BUF(ctx->device, loss_per_pos, static_cast<size_t>(n) * sizeof(double), "per-position losses");
   std::vector<ptycho::TileDesc> table(ntiles);
+  int64_t tile_bytes = 0;
   for (int k = 0; k < ntiles; ++k) {
     const ptycho_tile_desc& t = tiles[k];
     if (t.ty0 < 0 || t.tx0 < 0 || t.ty1 > H || t.tx1 > W || t.ty0 >= t.ty1 || t.tx0 >= t.tx1)
@@ -670,6 +671,7 @@ int tiles_grad_impl(ptycho_ctx* ctx, const void* obj, int32_t H, int32_t W, int6
     d.grad = static_cast<float2*>(t.grad);
     d.gslice = static_cast<long long>(t.eh) * t.ew;
     d.gld = t.ew;
+    tile_bytes += static_cast<int64_t>(ctx->S) * t.eh * t.ew * static_cast<int64_t>(sizeof(float2));
   }
   // Upload the table only when it changed (a walk passes the same tiles every step).  The copy is
   // stream-ordered after launches that still read the old table, and the host copy it reads is
@@ -701,7 +703,7 @@ int tiles_grad_impl(ptycho_ctx* ctx, const void* obj, int32_t H, int32_t W, int6
   a.ntiles = ntiles;
   a.probe_stride = probe_stride;
   if (n > 0) {
-    rc = launch_fused_timed(ctx, a, ptycho::kModeLossGrad);
+    rc = launch_fused_timed(ctx, a, ptycho::kModeLossGrad, tile_bytes);
     if (rc != PTYCHO_OK) return rc;
   }
   PT_HIP(ptycho::launch_finalize_loss(ctx->d_loss, n, loss, acc, ctx->stream));

@@ -135,7 +135,8 @@ struct BatchArgs {
   int* next;             // [8]
 };
 
-hipError_t launch_fused(const KernelArgs& a, int mode, int grid, hipStream_t st);
+// tile_bytes: of the tiles' gradients, for the all-tiles launch on one object
+hipError_t launch_fused(const KernelArgs& a, int mode, int grid, hipStream_t st, long long tile_bytes = 0);
 hipError_t launch_batch(const BatchArgs& a, int M, int grid, hipStream_t st);
 hipError_t launch_batch_finalize(const BatchRecon* recs, const double* item_loss, double* losses, double* hist,
                                  const int* iter, int hist_rows, int nrecon, hipStream_t st);

@@ -1201,20 +1201,24 @@ hipError_t launch_shift_probes(const float2* probe, const float* shifts, int n, 
   return hipGetLastError();
 }
 
-// Consecutive positions per workgroup (job_position).  Runs of 8 measured best while object and gradient fit
-// the 256 MiB Infinity Cache; beyond, the windows in flight on an XCD have to share what its L2 keeps, and
-// runs of 2 did.  Runs of 1 / 2 / 4 / 8 / 16: 4096 eight-slice positions on 1024^2 5.58 / 4.67 / 4.54 / 4.50 /
-// 4.57 ms, two slices 1.52 / 1.35 / 1.26 / 1.22 / 1.25 ms; 16632 16-slice positions on 2048^2 36.4 / 36.2 /
-// 36.5 / 36.9 / 37.8 ms.
-static int launch_run(const KernelArgs& a, int mode) {
+// Consecutive positions per workgroup (job_position).  Gradients take runs of 8: 1 / 2 / 4 / 8 / 16 took 5.58 /
+// 4.67 / 4.54 / 4.50 / 4.57 ms for 4096 eight-slice positions on 1024^2 and 1.52 / 1.35 / 1.26 / 1.22 / 1.25 ms
+// for two slices, and 2 / 8 on larger objects (object and gradient 0.35 to 1.1 GB) 11.4 / 10.9 ms for 8 x 1520^2,
+// 19.1 / 17.8 for 8 x 2048^2, 38.8 / 35.7 for 16 x 2048^2, 19.1 / 18.8 for 8 x 2900^2, 9.07 / 8.87 for 4 x 4096^2.
+// The all-tiles launch, whose gradient is spread over the tiles' boxes, takes 2 once object and boxes exceed 1 GiB:
+// 16 x 2048^2 on 4 x 4 tiles (1.29 GB) 35.2 / 36.2 ms; below, 16 x 1760^2 (1.04 GB) 31.2 / 30.8, 8 x 1760^2
+// (0.52 GB) 15.5 / 15.2, 8 x 1360^2 (0.32 GB) 9.10 / 9.01 (but 16 x 1440^2, 0.71 GB, 20.1 / 20.4).  Without a
+// gradient there is nothing to queue for, and runs of 2 and 8 are within one per cent.
+static int launch_run(const KernelArgs& a, int mode, long long tile_bytes) {
   if (sums_runs(a, mode)) return 1 << 20;  // one run per workgroup
-  const long long bytes = 2LL * a.S * a.bh * a.bw * static_cast<long long>(sizeof(float2));
-  return bytes <= (256LL << 20) ? 8 : 2;
+  if (mode != kModeLossGrad && mode != kModeLossGradProbe) return 2;
+  const long long object = a.S * static_cast<long long>(a.bh) * a.bw * static_cast<long long>(sizeof(float2));
+  return tile_bytes > 0 && object + tile_bytes > (1LL << 30) ? 2 : 8;
 }
 
-hipError_t launch_fused(const KernelArgs& args, int mode, int grid, hipStream_t st) {
+hipError_t launch_fused(const KernelArgs& args, int mode, int grid, hipStream_t st, long long tile_bytes) {
   KernelArgs a = args;
-  a.run = launch_run(a, mode);
+  a.run = launch_run(a, mode, tile_bytes);
   if (a.M == 128) return launch_fused_m<128>(a, mode, grid, st);
   if (a.M == 64) return launch_fused_m<64>(a, mode, grid, st);
   return hipErrorInvalidValue;

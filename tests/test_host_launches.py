@@ -172,3 +172,42 @@ done(r=r)
 ''')
     for rc, stitch, by_box in out["r"]:
         assert rc == 0 and stitch <= 2 * by_box, out
+
+
+def test_runs_of_positions_by_launch():
+    """Runs of 8 consecutive positions per workgroup for gradients, whatever the size of the object and also
+    for Alg. 1's batches; 2 for the all-tiles launch when object and boxes exceed 1 GiB, and without a gradient;
+    one whole run for the register sums."""
+    out = host_hip.run(STATES + r'''
+def runs():
+    return [int(x.split(" run ")[1]) for x in log() if "fused_kernel" in x]
+r = {}
+def objects(name, M, S, W):
+    rc, h = context(M, S, 5000)
+    log()
+    d = [device(8 * S * W * W + (1 << 20)) for _ in range(6)]
+    args = (h, d[0], W, W, c_int64(W * W), W, d[1], d[2], 5000, d[3])
+    rc |= L.ptycho_loss_grad(*args, d[4], None, d[5], c_int64(W * W), W, 0, None)
+    rc |= L.ptycho_loss(*args, d[4], None, 0)
+    rc |= L.ptycho_forward(*args[:9], d[5])
+    r[name] = [rc] + runs()
+def tiles(name, S, W, n):
+    rc, h = context(128, S, 5000)
+    bx = list(boxes(W, W, n, n, 64))
+    t = (Tile * (n * n))(*[Tile(*b, device(8 * S * b[6] * b[7])) for b in bx])
+    d = [device(8 * S * W * W + (1 << 20)) for _ in range(6)]
+    log()
+    rc |= L.ptycho_tiles_grad(h, d[0], W, W, c_int64(W * W), W, t, n * n, 64, d[1], d[2], d[3], 5000, d[4], d[5], None, 0)
+    s = states(S, bx)
+    seg = (c_int32 * (n * n + 1))(*[5000 * k // (n * n) for k in range(n * n + 1)])
+    rc |= step(h, s, seg, 5000)
+    r[name] = [rc] + runs()
+objects("small", 128, 8, 512)
+objects("large", 128, 8, 4096)
+objects("sums", 64, 1, 512)
+tiles("few", 8, 1024, 2)
+tiles("many", 16, 2048, 4)
+done(**r)
+''')
+    assert out == {"small": [0, 8, 2, 2], "large": [0, 8, 2, 2], "sums": [0, 1 << 20, 2, 2], "few": [0, 8, 8],
+                   "many": [0, 2, 8]}
