@@ -21,7 +21,7 @@ __host__ __device__ constexpr int ws_slots(int S, int ck) {
                 : ((S - 1) / ck) + ((ck < S ? ck : S) - 1) + (((S - 1) / ck) > 0 && ck > 1 ? 1 : 0);
 }
 
-// Workgroups of the position kernels that share a CU: a 128-window workgroup (8 waves, 136 KB of LDS)
+// Workgroups of the position kernels that share a CU: a 128-window workgroup (8 waves, 135 KB of LDS)
 // fills one alone; three 64-window workgroups (4 waves, 35 KB of LDS and at most 168 VGPRs each) fit.
 __host__ __device__ constexpr int fused_workgroups_per_cu(int M) { return M == 64 ? 3 : 1; }
 

@@ -16,6 +16,8 @@
 // atomics; the lanes are rolled to the gradient's 128-byte lines, so each
 // instruction covers two whole lines.  Optional
 // outputs: the probe gradient (per-workgroup partial sums).
+#include <type_traits>
+
 #include "fft_lds.hpp"
 #include "ptycho_kernels.h"
 
@@ -466,7 +468,10 @@ struct Shared {
   float2 lds[G::LDS_ELEMS];
   float2 hx[G::M];
   double red[G::T / 64];
-  float2 tw[G::M];         // SUM: the pass-B twiddles, read again for each transform
+};
+template <class G>
+struct SharedSum : Shared<G> {
+  float2 tw[G::M];  // the pass-B twiddles, read again for each transform
 };
 
 // Loads the separable propagator factor of a reconstruction: the x part into
@@ -494,8 +499,9 @@ __device__ __forceinline__ float2 load_propagator(Shared<G>& sh, const float2* _
 // batched one).
 // SUM: single-slice positions whose gradients are summed in registers.
 template <class G, int MODE, bool LINES = false, bool CKPT = false, bool AHEAD = false, bool SUM = false>
-__device__ __forceinline__ double run_position(const PositionJob& jb, Shared<G>& sh, const float2 (&twb)[G::X1],
-                                               float2 hy, float2* __restrict__ ws, const Lanes<G>& L,
+__device__ __forceinline__ double run_position(const PositionJob& jb,
+                                               std::conditional_t<SUM, SharedSum<G>, Shared<G>>& sh,
+                                               const float2 (&twb)[G::X1], float2 hy, float2* __restrict__ ws, const Lanes<G>& L,
                                                RowSum<G>* sum = nullptr) {
   constexpr bool GRAD = MODE == kModeLossGrad || MODE == kModeLossGradProbe;
   constexpr bool LOSS = MODE != kModeIntensity;
@@ -735,7 +741,7 @@ template <int M, int MODE, bool SUM = false, bool LIST = false>
 __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(KernelArgs a) {
   using G = Geo<M>;
   constexpr bool LOSS = MODE != kModeIntensity;
-  __shared__ Shared<G> sh;
+  __shared__ std::conditional_t<SUM, SharedSum<G>, Shared<G>> sh;
   Lanes<G> L;
   float2 twb[G::X1];
   load_twb<G>(twb, a.tw, L.m2);
