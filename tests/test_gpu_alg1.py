@@ -182,3 +182,40 @@ def test_more_patterns_than_positions():
     d = problem(spec)
     t, alpha, walk = _walk(spec, d, 8, 2, extra=3)
     _matches_oracle(spec, d, t, alpha, walk, 8, 2)
+
+
+def _scattered(M, S, H_W, n, tiles, halo, seed, within=None):
+    """n positions at random (window centres below `within` of the object's width only, when given)."""
+    spec = ps.with_overrides(ps.workload("2d-256-m64" if M == 64 else "ms8-1024-m128"), W=H_W, S=S, ny=2, nx=2, step=4,
+                             tiles=tiles, halo=halo, noise=False)
+    d = ps.build_inputs(spec)
+    d["H"] = oracle.fresnel_propagator(spec.M, spec.wavelength_A, spec.dz_A, spec.pixel_A)
+    rng = np.random.default_rng(seed)
+    top = H_W - M
+    pos = np.stack([rng.integers(0, top + 1, n), rng.integers(0, (top if within is None else within) + 1, n)], 1)
+    d["pos"] = np.ascontiguousarray(pos, dtype=np.int32)
+    d["meas"] = oracle.forward(d["obj_true"], d["probe"], d["pos"], d["H"]).astype(np.float32)
+    return spec, d
+
+
+@pytest.mark.parametrize("M,S,W,n,tiles,halo,batch,T,within", [
+    (128, 2, 301, 420, (2, 2), 64, 150, 1, None),  # odd boxes (atomics staged), more jobs than workgroups
+    (128, 3, 304, 300, (2, 1), 64, 200, 2, None),  # boxes of a whole number of lines, rolled
+    (64, 1, 190, 2500, (2, 2), 33, 900, 1, None),  # register sums across tiles, runs of several jobs
+    (64, 1, 192, 900, (2, 3), 32, 1, 40, None),    # a position at a time
+    (64, 2, 600, 150, (1, 2), 40, 20, 3, 200),     # rows wider than a step of the update; a tile without positions
+])
+def test_walk_over_launch_shapes(M, S, W, n, tiles, halo, batch, T, within):
+    """Batches that give a workgroup several jobs, of several tiles with boxes of their own width; odd and
+    whole-line boxes, one and more slices, tiles without positions and batches of uneven size."""
+    import torch
+    say(f"Alg. 1, M={M} S={S} W={W} n={n} tiles {tiles} batch {batch}")
+    spec, d = _scattered(M, S, W, n, tiles, halo, 17, within)
+    t = to_dev(d)
+    plan = TileWalk(d["pos"], W, W, M, tiles, halo)
+    alpha = 0.5 * oracle.gd_step_size(d["probe"], d["pos"], W, W, S)
+    meas = t["meas"][torch.tensor(plan.order, device="cuda:0")]
+    walk = Alg1Walk(context(spec, n), plan, t["obj"], t["probe"], meas, alpha, batch, T)
+    if within is not None:
+        assert min(p.hi - p.lo for p in plan.plans) == 0
+    _matches_oracle(spec, d, t, alpha, walk, batch, T)

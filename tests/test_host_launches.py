@@ -197,7 +197,8 @@ def tiles(name, S, W, n):
     t = (Tile * (n * n))(*[Tile(*b, device(8 * S * b[6] * b[7])) for b in bx])
     d = [device(8 * S * W * W + (1 << 20)) for _ in range(6)]
     log()
-    rc |= L.ptycho_tiles_grad(h, d[0], W, W, c_int64(W * W), W, t, n * n, 64, d[1], d[2], d[3], 5000, d[4], d[5], None, 0)
+    rc |= L.ptycho_tiles_grad(h, d[0], W, W, c_int64(W * W), W, t, n * n, 64, d[1], d[2], d[3], 5000, d[4], d[5], None,
+                              0)
     s = states(S, bx)
     seg = (c_int32 * (n * n + 1))(*[5000 * k // (n * n) for k in range(n * n + 1)])
     rc |= step(h, s, seg, 5000)
@@ -211,3 +212,54 @@ done(**r)
 ''')
     assert out == {"small": [0, 8, 2, 2], "large": [0, 8, 2, 2], "sums": [0, 1 << 20, 2, 2], "few": [0, 8, 8],
                    "many": [0, 2, 8]}
+
+
+def test_alg1_calls_refuse_bad_arguments():
+    """The batch step and the flush check their tiles, segments and sizes on the host and enqueue nothing when
+    they refuse."""
+    out = host_hip.run(STATES + r'''
+rc, h = context(64, 2, 10)
+bx = list(boxes(256, 256, 2, 2, 32))
+good = states(2, bx)
+dev = [device(4 << 20) for _ in range(7)]
+def call(tiles=good, n=4, lists=8, seg=(0, 2, 4, 6, 8), step=0.1, total=100, null=None, ctx=h):
+    a = [None if i == null else p for i, p in enumerate(dev)]
+    s = (c_int32 * len(seg))(*seg) if seg else None
+    return L.ptycho_tiles_batch_step(ctx, tiles, n, a[0], a[1], a[2], a[3], total, a[4], lists, a[5], s, c_float(step),
+                                     a[6])
+def flush(tiles=good, ny=2, nx=2, step=0.1, ctx=h):
+    return L.ptycho_tiles_flush(ctx, tiles, ny, nx, c_float(step))
+def changed(k, **fields):
+    t = states(2, bx)
+    for f, v in fields.items():
+        setattr(t[k], f, v)
+    return t
+log()
+inf = float("inf")
+r = dict(
+    context=call(ctx=None), tiles=call(tiles=None), none=call(n=0), step=call(step=inf),
+    total=call(total=-1), negative=call(lists=-1),
+    capacity=call(lists=11, seg=(0, 2, 4, 6, 11)), segments=call(seg=None), short=call(seg=(0, 2, 4, 6, 7)),
+    first=call(seg=(1, 2, 4, 6, 8)), decrease=call(seg=(0, 4, 2, 6, 8)),
+    nulls=[call(null=i) for i in range(7)],
+    shared=call(tiles=changed(1, acc=good[1].acc, grad=good[1].acc)),
+    overlap=call(tiles=changed(2, obj=good[2].obj + 8, acc=good[2].obj)),
+    buffer=call(tiles=changed(0, acc=None)), outside=call(tiles=changed(0, ty0=-1)), box=call(tiles=changed(0, eh=0)),
+    far=call(tiles=changed(0, ey0=2**31 - 10, ty0=2**31 - 10, ty1=2**31 - 1)),
+    small=call(tiles=changed(3, ey0=192, ty0=192, ty1=255, eh=63)),
+    flush=[flush(ctx=None), flush(tiles=None), flush(ny=0), flush(nx=70000), flush(step=-inf),
+           flush(tiles=changed(1, grad=good[1].obj, obj=good[1].obj))])
+l = log()
+ok = [call(lists=0, seg=(0,) * 5), call(), flush(),
+      call(tiles=changed(3, ey0=192, ty0=192, ty1=255, eh=63), lists=6, seg=(0, 2, 4, 6, 6))]
+done(log=l, ok=ok, launches=len(log()), **r)
+''')
+    arg, shape, halo, capacity = -1, -2, -4, -9
+    assert out["log"] == []
+    assert out["ok"] == [0] * 4 and out["launches"] > 0
+    for name in ("context", "tiles", "none", "step", "total", "negative", "segments", "short", "first", "decrease",
+                 "shared", "overlap", "buffer"):
+        assert out[name] == arg, name
+    assert out["nulls"] == [arg] * 7 and out["flush"] == [arg] * 6
+    assert out["capacity"] == capacity and out["small"] == halo
+    assert out["outside"] == out["box"] == out["far"] == shape
