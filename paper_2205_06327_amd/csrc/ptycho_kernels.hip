@@ -1214,11 +1214,13 @@ hipError_t launch_shift_probes(const float2* probe, const float* shifts, int n, 
 // The all-tiles launch, whose gradient is spread over the tiles' boxes, takes 2 once object and boxes exceed 1 GiB:
 // 16 x 2048^2 on 4 x 4 tiles (1.29 GB) 35.2 / 36.2 ms; below, 16 x 1760^2 (1.04 GB) 31.2 / 30.8, 8 x 1760^2
 // (0.52 GB) 15.5 / 15.2, 8 x 1360^2 (0.32 GB) 9.10 / 9.01 (but 16 x 1440^2, 0.71 GB, 20.1 / 20.4).  Without a
-// gradient there is nothing to queue for, and runs of 2 and 8 are within one per cent.
+// gradient little depends on it: 2 / 8 took 31.3 / 30.4 us for 3600 single-slice patterns of 64-windows on 700^2,
+// 119.3 / 118.2 for 4900 of three slices, 3294 / 3312 us for 10000 eight-slice ones of 128-windows on 1520^2
+// (0.15 GB), 5325 / 5335 for 16384 on 2048^2; the line is where the larger objects begin.
 static int launch_run(const KernelArgs& a, int mode, long long tile_bytes) {
   if (sums_runs(a, mode)) return 1 << 20;  // one run per workgroup
-  if (mode != kModeLossGrad && mode != kModeLossGradProbe) return 2;
   const long long object = a.S * static_cast<long long>(a.bh) * a.bw * static_cast<long long>(sizeof(float2));
+  if (mode != kModeLossGrad && mode != kModeLossGradProbe) return object > (128LL << 20) ? 2 : 8;
   return tile_bytes > 0 && object + tile_bytes > (1LL << 30) ? 2 : 8;
 }
 

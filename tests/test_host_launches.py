@@ -176,8 +176,8 @@ done(r=r)
 
 def test_runs_of_positions_by_launch():
     """Runs of 8 consecutive positions per workgroup for gradients, whatever the size of the object and also
-    for Alg. 1's batches; 2 for the all-tiles launch when object and boxes exceed 1 GiB, and without a gradient;
-    one whole run for the register sums."""
+    for Alg. 1's batches; 2 for the all-tiles launch when object and boxes exceed 1 GiB, and without a gradient
+    for objects over 128 MiB; one whole run for the register sums."""
     out = host_hip.run(STATES + r'''
 def runs():
     return [int(x.split(" run ")[1]) for x in log() if "fused_kernel" in x]
@@ -210,7 +210,7 @@ tiles("few", 8, 1024, 2)
 tiles("many", 16, 2048, 4)
 done(**r)
 ''')
-    assert out == {"small": [0, 8, 2, 2], "large": [0, 8, 2, 2], "sums": [0, 1 << 20, 2, 2], "few": [0, 8, 8],
+    assert out == {"small": [0, 8, 8, 8], "large": [0, 8, 2, 2], "sums": [0, 1 << 20, 8, 8], "few": [0, 8, 8],
                    "many": [0, 2, 8]}
 
 
