@@ -1120,8 +1120,10 @@ __global__ void __launch_bounds__(64 * kReduceWaves) probe_reduce_kernel(const f
 // launchers (host side)
 // ---------------------------------------------------------------------------
 // Single-slice gradients of 64-windows are summed in registers along a workgroup's run (RowSum): 297 -> 179 us
-// for 9216 positions, 87 -> 63 us for 2550, 24 -> 22 us for 256.  128-windows keep adding each window: their
-// sum (64 VGPRs) left the losses a rounding away from those of every other gradient launch.
+// for 9216 positions, 87 -> 63 us for 2550, 24 -> 22 us for 256, in scan rows.  Orders that leave the row at every
+// position send each window whole and gain nothing by it: column by column 298 us, at random 307.  128-windows
+// keep adding each window: their sum (64 VGPRs) needs the pass-B twiddles from LDS, and the compiler then rounds
+// other products than in the other gradient launches (losses 2e-11 to 4e-10 apart).
 static bool sums_runs(const KernelArgs& a, int mode) { return a.M == 64 && a.S == 1 && mode == kModeLossGrad; }
 
 template <int M, int MODE, bool SUM = false, bool LIST = false>

@@ -11,7 +11,11 @@ namespace ptycho {
 namespace {
 
 constexpr int kWaves = 4;  // waves per workgroup; a wave walks rows, its lanes columns
-constexpr int kCols = 4;   // columns per lane and step, loaded together
+constexpr int kCols = 4;   // columns per lane and step of the updates, loaded together
+// The same of the box lists.  2 / 4 / 8 / 10 took 589 / 580 / 577 / 570 us for neighbour addition and stitch of
+// 16 boxes 640 wide (16 slices), 206 / 192 / 180 / 181 for 320 to 384 wide, 481 / 471 / 465 / 463 for 4 boxes 1088
+// wide, 204 / 195 / 188 / 189 for 950 wide (8 slices); for narrower or fewer values they are alike.
+constexpr int kBoxCols = 10;
 
 // One box operation per (blockIdx.y / S), one slice of it per blockIdx.y % S.
 // Bound: the bytes of the boxes.  The neighbour addition of 16 boxes of 640^2 x
@@ -20,39 +24,38 @@ constexpr int kCols = 4;   // columns per lane and step, loaded together
 // launches and 0.57 ms (3.6 TB/s); the sum of the 16 boxes into the gradient
 // 0.56 ms as a fill and 16 additions, 0.27 ms as a list.
 __global__ void __launch_bounds__(64 * kWaves) box_list_kernel(BoxList list, int S) {
-  constexpr int kCols = 10;  // 4 / 8 / 10 took 581 / 578 / 570 us for neighbour addition and stitch
   const int o = static_cast<int>(blockIdx.y) / S, s = static_cast<int>(blockIdx.y) % S;
   const BoxOp op = list.op[o];
   const int lane = static_cast<int>(threadIdx.x & 63);
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   for (int y = static_cast<int>(blockIdx.x) * kWaves + wave; y < op.h; y += static_cast<int>(gridDim.x) * kWaves) {
     float2* __restrict__ drow = op.dst + s * op.slice + static_cast<long long>(y) * op.ld;
-    for (int xb = lane; xb < op.w; xb += 64 * kCols) {
-      float2 a[kCols];
+    for (int xb = lane; xb < op.w; xb += 64 * kBoxCols) {
+      float2 a[kBoxCols];
       if (op.init == kBoxAdd) {
-        for (int k = 0; k < kCols; ++k) a[k] = xb + 64 * k < op.w ? drow[xb + 64 * k] : make_float2(0.f, 0.f);
+        for (int k = 0; k < kBoxCols; ++k) a[k] = xb + 64 * k < op.w ? drow[xb + 64 * k] : make_float2(0.f, 0.f);
       } else {
-        for (int k = 0; k < kCols; ++k) a[k] = make_float2(0.f, 0.f);
+        for (int k = 0; k < kBoxCols; ++k) a[k] = make_float2(0.f, 0.f);
       }
       for (int i = 0; i < op.nsrc; ++i) {
         const BoxSrc& src = list.src[op.first + i];
         if (y < src.y0 || y >= src.y1) continue;  // uniform
         const float2* __restrict__ srow = src.p + s * src.slice + static_cast<long long>(y) * src.ld;
-        float2 v[kCols];
-        bool in[kCols];
-        for (int k = 0; k < kCols; ++k) {
+        float2 v[kBoxCols];
+        bool in[kBoxCols];
+        for (int k = 0; k < kBoxCols; ++k) {
           const int x = xb + 64 * k;
           in[k] = x >= src.x0 && x < src.x1;
           v[k] = in[k] ? srow[x] : make_float2(0.f, 0.f);
         }
         if (op.init == kBoxCopy && i == 0) {
-          for (int k = 0; k < kCols; ++k) a[k] = v[k];
+          for (int k = 0; k < kBoxCols; ++k) a[k] = v[k];
         } else {
-          for (int k = 0; k < kCols; ++k)
+          for (int k = 0; k < kBoxCols; ++k)
             if (in[k]) a[k] = make_float2(a[k].x + v[k].x, a[k].y + v[k].y);
         }
       }
-      for (int k = 0; k < kCols; ++k)
+      for (int k = 0; k < kBoxCols; ++k)
         if (xb + 64 * k < op.w) drow[xb + 64 * k] = a[k];
     }
   }
