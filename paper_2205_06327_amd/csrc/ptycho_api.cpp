@@ -893,7 +893,8 @@ Rect box_of(const ptycho_tile_desc& t) { return {t.ey0, t.ey0 + t.eh, t.ex0, t.e
 Rect tile_of(const ptycho_tile_desc& t) { return {t.ty0, t.ty1, t.tx0, t.tx1}; }
 
 // Rectangles inside H x W, found by place: a table of cells about the size of a mean tile lists the
-// rectangles that reach into each.  All pairs of 4096 tiles and their boxes took 64 ms of host time per stitch, this 1.6.
+// rectangles that reach into each.  All pairs of 4096 tiles and their boxes took 64 ms of host time per
+// stitch, this 1.6.
 class Places {
  public:
   Places(int H, int W, const ptycho_tile_desc* tiles, int n) {
@@ -905,8 +906,8 @@ class Places {
     ch_ = static_cast<int>(std::max<int64_t>(1, h / n));
     cw_ = static_cast<int>(std::max<int64_t>(1, w / n));
     while ((H / ch_ + 1LL) * (W / cw_ + 1LL) > 4LL * n + 64) {  // few cells, however uneven the tiles
-      ch_ = std::min(2LL * ch_, H + 1LL);
-      cw_ = std::min(2LL * cw_, W + 1LL);
+      ch_ = static_cast<int>(std::min<int64_t>(2LL * ch_, H));
+      cw_ = static_cast<int>(std::min<int64_t>(2LL * cw_, W));
     }
     nx_ = W / cw_ + 1;
     cells_.resize(static_cast<size_t>(H / ch_ + 1) * nx_);

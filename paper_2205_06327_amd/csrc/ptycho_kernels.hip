@@ -501,8 +501,8 @@ __device__ __forceinline__ float2 load_propagator(Shared<G>& sh, const float2* _
 template <class G, int MODE, bool LINES = false, bool CKPT = false, bool AHEAD = false, bool SUM = false>
 __device__ __forceinline__ double run_position(const PositionJob& jb,
                                                std::conditional_t<SUM, SharedSum<G>, Shared<G>>& sh,
-                                               const float2 (&twb)[G::X1], float2 hy, float2* __restrict__ ws, const Lanes<G>& L,
-                                               RowSum<G>* sum = nullptr) {
+                                               const float2 (&twb)[G::X1], float2 hy, float2* __restrict__ ws,
+                                               const Lanes<G>& L, RowSum<G>* sum = nullptr) {
   constexpr bool GRAD = MODE == kModeLossGrad || MODE == kModeLossGradProbe;
   constexpr bool LOSS = MODE != kModeIntensity;
   const int S = SUM ? 1 : jb.S;
@@ -786,7 +786,7 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
     const int y0 = gy - a.oy, x0 = gx - a.ox;
     bool ok;
     jb.win = a.obj + static_cast<long long>(y0) * a.ld + x0;
-    if (MODE == kModeLossGrad && a.tiles != nullptr) {  // all-tiles mode: the owning tile's box and gradient buffer (uniform)
+    if (MODE == kModeLossGrad && a.tiles != nullptr) {  // all-tiles mode: the owning tile's box and buffer (uniform)
       const int tk = a.tile_of_pos[q];
       ok = tk >= 0 && tk < a.ntiles;
       // listed under the tile that owns it: the update that consumes the gradient goes by the list
