@@ -78,7 +78,7 @@ enum {
   PTYCHO_E_ASSIGN = -5,       /* a window centre lies outside its tile */
   PTYCHO_E_UNSUPPORTED = -6,  /* unsupported window size or slice count */
   PTYCHO_E_HIP = -7,          /* HIP runtime error */
-  PTYCHO_E_NOMEM = -8,        /* device allocation failed (create/reserve only) */
+  PTYCHO_E_NOMEM = -8,        /* device allocation failed (where something is allocated: see Ownership) */
   PTYCHO_E_CAPACITY = -9      /* more positions than the context reserved */
 };
 

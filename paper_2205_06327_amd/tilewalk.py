@@ -531,7 +531,9 @@ class Alg1Walk:
     cleared.  With batch = 1 this is the per-probe loop of Alg. 1.  The tiles
     of a batch are independent, so one launch takes all of them
     (ptycho_tiles_batch_step): a tile's batch alone, often fewer positions
-    than CUs, would leave most of the device idle.  ``lanes`` is accepted for
+    than CUs, would leave most of the device idle.  An iteration is launches on
+    the caller's stream only, the first one too, so it can be captured; between
+    replays the context is free for other calls.  ``lanes`` is accepted for
     callers that set it; the tiles share their launches whatever its value.
     """
 
