@@ -479,12 +479,12 @@ int ptycho_tiles_passes(ptycho_ctx* ctx, const ptycho_tile_desc* tiles, int32_t 
  * its own (tile_of_pos) PTYCHO_STATUS_ASSIGN.  n must not exceed the reserved
  * capacity.
  *
- * The tiles travel in the arguments of the launches, which replace the
- * context's table of them: nothing depends on an earlier call, so both calls
- * can be captured without a first run, and a replay does not mind what ran on
- * the context in between.  They allocate only where the tiles outgrow the
- * table (more than 4096, then twice as many, ...); outgrown tables live as
- * long as the context.
+ * The tiles travel in the arguments of the launches: nothing depends on an
+ * earlier call, so both calls can be captured without a first run, and a
+ * replay does not mind what ran on the context in between.  More than 48 tiles
+ * go through a table of the context, which every batch step writes anew; it is
+ * allocated again only where the tiles outgrow it (more than 4096, then twice
+ * as many, ...), and outgrown tables live as long as the context.
  *
  * ptycho_tiles_flush: the directional passes on the AccBufs, then
  * V -= step * AccBuf and AccBuf = 0 for every tile.

@@ -107,7 +107,7 @@ struct ptycho_ctx {
   int parts = 0;                   // at least grid
   ptycho::TileDesc* d_tiles = nullptr;  // tile table of ptycho_tiles_grad (kMaxTiles entries)
   std::vector<ptycho::TileDesc> h_tiles;
-  ptycho::TileDesc* d_states = nullptr;  // tile table of Alg. 1, written by every call that uses it
+  ptycho::TileDesc* d_states = nullptr;  // tile table of Alg. 1's batches, written by every call that uses it
   size_t states_cap = ptycho::kMaxTiles;
   std::vector<ptycho::TileDesc*> old_states;  // outgrown tables: captured launches may still use them
   float2* d_ws = nullptr;  // incident-wave store, grid * ws_slots(S, ck) * M*M
@@ -234,13 +234,14 @@ ptycho::KernelArgs base_args(const ptycho_ctx* c) {
 }
 
 // Launch of a fused kernel, bracketed by timing events when profiling.
-int launch_fused_timed(ptycho_ctx* c, const ptycho::KernelArgs& a, int mode, int64_t tile_bytes = 0) {
+int launch_fused_timed(ptycho_ctx* c, const ptycho::KernelArgs& a, int mode, int64_t tile_bytes = 0,
+                       const ptycho::TileChunk* chunk = nullptr) {
   const bool stores = mode == ptycho::kModeLossGrad || mode == ptycho::kModeLossGradProbe;
   const int grid = std::min(a.n, stores ? c->grid : most_workgroups(c));
   const bool timed = c->profiling && c->ev_used < c->ev_n.size();
   if (c->profiling && !timed) ++c->dropped;
   if (timed) PT_HIP(hipEventRecord(c->ev[2 * c->ev_used], c->stream));
-  PT_HIP(ptycho::launch_fused(a, mode, grid, c->stream, tile_bytes));
+  PT_HIP(ptycho::launch_fused(a, mode, grid, c->stream, tile_bytes, chunk));
   if (timed) {
     PT_HIP(hipEventRecord(c->ev[2 * c->ev_used + 1], c->stream));
     c->ev_n[c->ev_used++] = a.n;
@@ -1181,10 +1182,17 @@ int tile_states(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int32_t n, std:
   return check_disjoint(r);
 }
 
-// Puts the tiles into the context's device table, in the arguments of launches: nothing is left from an
-// earlier call, so calls can be captured at any time and replayed whatever ran in between, and walks that
-// take turns do not wait for each other.
-int write_states(ptycho_ctx* ctx, const std::vector<ptycho::TileDesc>& table) {
+// The tiles of a batch's gradient launch: in its arguments, or, when there are more than they hold, in the
+// context's device table, written by launches that carry them.  Nothing is left from an earlier call, so calls
+// can be captured at any time and replayed whatever ran in between, and walks that take turns do not wait for
+// each other.
+int pass_states(ptycho_ctx* ctx, const std::vector<ptycho::TileDesc>& table, ptycho::TileChunk* chunk,
+                const ptycho::TileDesc** dev) {
+  *dev = nullptr;
+  if (table.size() <= ptycho::TileChunk::kTiles) {
+    std::copy(table.begin(), table.end(), chunk->t);
+    return PTYCHO_OK;
+  }
   if (table.size() > ctx->states_cap) {
     ptycho::TileDesc* d = nullptr;
     const size_t cap = std::max(table.size(), 2 * ctx->states_cap);
@@ -1196,6 +1204,7 @@ int write_states(ptycho_ctx* ctx, const std::vector<ptycho::TileDesc>& table) {
     ctx->bytes += static_cast<int64_t>(cap * sizeof(ptycho::TileDesc));
   }
   PT_HIP(ptycho::launch_set_tiles(table.data(), static_cast<int>(table.size()), ctx->d_states, ctx->stream));
+  *dev = ctx->d_states;
   return PTYCHO_OK;
 }
 }  // namespace
@@ -1226,9 +1235,10 @@ int ptycho_tiles_batch_step(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int
   PT_BUF(ctx->device, index, static_cast<size_t>(n) * sizeof(int32_t), "batch positions");
   PT_BUF(ctx->device, segments, (static_cast<size_t>(ntiles) + 1) * sizeof(int32_t), "segments");
   PT_BUF(ctx->device, losses, static_cast<size_t>(ntiles) * sizeof(double), "losses");
-  if ((rc = write_states(ctx, table)) != PTYCHO_OK) return rc;
   if (n > 0) {
     ptycho::KernelArgs a = base_args(ctx);
+    ptycho::TileChunk chunk;
+    if ((rc = pass_states(ctx, table, &chunk, &a.tiles)) != PTYCHO_OK) return rc;
     a.n = n;
     a.oob_flag = PTYCHO_STATUS_HALO;
     a.probe = static_cast<const float2*>(probe);
@@ -1237,13 +1247,12 @@ int ptycho_tiles_batch_step(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int
     a.total = total;
     a.seg = segments;
     a.meas = meas;
-    a.tiles = ctx->d_states;
     a.tile_of_pos = tile_of_pos;
     a.ntiles = ntiles;
-    rc = launch_fused_timed(ctx, a, ptycho::kModeLossGrad);
+    rc = launch_fused_timed(ctx, a, ptycho::kModeLossGrad, 0, &chunk);
     if (rc != PTYCHO_OK) return rc;
   }
-  PT_HIP(ptycho::launch_tile_step(ctx->d_states, ntiles, ctx->S, ctx->M, pos, tile_of_pos, total, index, n, segments,
+  PT_HIP(ptycho::launch_tile_step(table.data(), ntiles, ctx->S, ctx->M, pos, tile_of_pos, total, index, n, segments,
                                   step, ctx->d_loss, losses, ctx->stream));
   return PTYCHO_OK;
 }
@@ -1261,9 +1270,8 @@ int ptycho_tiles_flush(ptycho_ctx* ctx, const ptycho_tile_state* tiles, int32_t 
     const ptycho_tile_state& t = tiles[k];
     acc[k] = {t.ty0, t.ty1, t.tx0, t.tx1, t.ey0, t.ex0, t.eh, t.ew, t.acc};
   }
-  if ((rc = write_states(ctx, table)) != PTYCHO_OK) return rc;
   if ((rc = enqueue_passes(ctx, acc, tiles_y, tiles_x)) != PTYCHO_OK) return rc;
-  PT_HIP(ptycho::launch_tile_flush(ctx->d_states, n, ctx->S, step, ctx->stream));
+  PT_HIP(ptycho::launch_tile_flush(table.data(), n, ctx->S, step, ctx->stream));
   return PTYCHO_OK;
 }
 

@@ -31,11 +31,11 @@ struct TileDesc {
   int ey0, ex0, eh, ew;    // extended box
   float2* grad;            // [S][eh][ew] dense
   long long gslice, gld;
-  float2* obj;             // the tile's own object copy (layout of grad), or null: the launch's object
+  float2* obj;             // Alg. 1: the tile's own object copy (layout of grad)
   float2* acc;             // accumulation buffer of Alg. 1 (layout of grad), or null
 };
 constexpr int kMaxTiles = 4096;
-// Tiles of one launch that writes a tile table.
+// Tiles that travel in the arguments of a launch.
 struct TileChunk {
   static constexpr int kTiles = 48;
   TileDesc t[kTiles];
@@ -97,8 +97,9 @@ struct KernelArgs {
   const TileDesc* tiles;
   const int* tile_of_pos;
   int ntiles;
-  // with index (and tiles): entries of pos, meas and tile_of_pos, and the jobs [seg[k], seg[k+1]) of tile k;
-  // other indices, and jobs listed under another tile than their own, are skipped
+  // with index: entries of pos, meas and tile_of_pos, and the jobs [seg[k], seg[k+1]) of tile k; other
+  // indices, and jobs listed under another tile than their own, are skipped.  The tiles are those of the
+  // launch's TileChunk, or of `tiles` when there are more than it holds.
   int total;
   const int* seg;        // [ntiles + 1]
 };
@@ -135,8 +136,9 @@ struct BatchArgs {
   int* next;             // [8]
 };
 
-// tile_bytes: of the tiles' gradients, for the all-tiles launch on one object
-hipError_t launch_fused(const KernelArgs& a, int mode, int grid, hipStream_t st, long long tile_bytes = 0);
+// tile_bytes: of the tiles' gradients, for the all-tiles launch on one object; chunk: the tiles of a launch with index
+hipError_t launch_fused(const KernelArgs& a, int mode, int grid, hipStream_t st, long long tile_bytes = 0,
+                        const TileChunk* chunk = nullptr);
 hipError_t launch_batch(const BatchArgs& a, int M, int grid, hipStream_t st);
 hipError_t launch_batch_finalize(const BatchRecon* recs, const double* item_loss, double* losses, double* hist,
                                  const int* iter, int hist_rows, int nrecon, hipStream_t st);
@@ -157,7 +159,8 @@ hipError_t launch_potential(int mode, float sigma, int S, int H, int W, const fl
 hipError_t launch_box_exchange(const float2* src, long long sslice, long long sld, float2* dst, long long dslice,
                                long long dld, int S, int oh, int ow, bool replace, float alpha, hipStream_t st);
 hipError_t launch_box_list(const BoxList& list, int S, int rows, hipStream_t st);
-hipError_t launch_set_tiles(const TileDesc* host, int ntiles, TileDesc* dev, hipStream_t st);
+// tiles: on the host
+hipError_t launch_set_tiles(const TileDesc* tiles, int ntiles, TileDesc* dev, hipStream_t st);
 hipError_t launch_tile_step(const TileDesc* tiles, int ntiles, int S, int M, const int* pos, const int* tile_of_pos,
                             int total, const int* index, int n, const int* seg, float step, const double* loss_work,
                             double* losses, hipStream_t st);

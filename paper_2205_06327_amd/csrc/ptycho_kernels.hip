@@ -734,11 +734,36 @@ __device__ __forceinline__ double run_position(const PositionJob& jb,
 template <int M>
 constexpr int kWavesPerSimd = fused_workgroups_per_cu(M) * Geo<M>::T / 256;
 
+// The object and gradient windows of the position (gy, gx) in the box of the tile that owns it, which has its
+// own object, laid out as its gradient; false, with the status bit, where they do not fit.  (The launches without
+// a list have the same checks written out: through this function 4096 single-slice 128-windows take 577 us
+// instead of 568.)
+template <int M>
+__device__ __forceinline__ bool take_tile(const TileDesc& T, int gy, int gx, PositionJob& jb, unsigned& flag) {
+  const int cy = gy + M / 2, cx = gx + M / 2;
+  bool ok = cy >= T.ty0 && cy < T.ty1 && cx >= T.tx0 && cx < T.tx1;
+  if (ok) {
+    ok = gy >= T.ey0 && gx >= T.ex0 && gy + M <= T.ey0 + T.eh && gx + M <= T.ex0 + T.ew;
+    flag = 2u;
+  }
+  if (ok) {
+    jb.grad = T.grad + static_cast<long long>(gy - T.ey0) * T.gld + (gx - T.ex0);
+    jb.gld = T.gld;
+    jb.gslice = T.gslice;
+    jb.win = T.obj + (jb.grad - T.grad);
+    jb.ld = T.gld;
+    jb.sstride = T.gslice;
+  }
+  return ok;
+}
+
 // LIST: jobs through a list of positions grouped by tile (KernelArgs::index, seg).  Kernels of their own: the
 // checks of the list in the others cost registers that the 128-window gradient does not have (4096
 // single-slice positions 566 -> 600 us).
+struct NoTiles {};
 template <int M, int MODE, bool SUM = false, bool LIST = false>
-__global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(KernelArgs a) {
+__global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(
+    KernelArgs a, std::conditional_t<LIST, TileChunk, NoTiles> chunk) {
   using G = Geo<M>;
   constexpr bool LOSS = MODE != kModeIntensity;
   __shared__ std::conditional_t<SUM, SharedSum<G>, Shared<G>> sh;
@@ -786,28 +811,29 @@ __global__ void __launch_bounds__(Geo<M>::T, kWavesPerSimd<M>) fused_kernel(Kern
     const int y0 = gy - a.oy, x0 = gx - a.ox;
     bool ok;
     jb.win = a.obj + static_cast<long long>(y0) * a.ld + x0;
-    if (MODE == kModeLossGrad && a.tiles != nullptr) {  // all-tiles mode: the owning tile's box and buffer (uniform)
+    // all-tiles mode: the owning tile's box and buffer (uniform)
+    if (LIST || (MODE == kModeLossGrad && a.tiles != nullptr)) {
       const int tk = a.tile_of_pos[q];
       ok = tk >= 0 && tk < a.ntiles;
       // listed under the tile that owns it: the update that consumes the gradient goes by the list
       if (LIST && ok) ok = p >= a.seg[tk] && p < a.seg[tk + 1];
       unsigned flag = 4u;
       if (ok) {
-        const TileDesc& T = a.tiles[tk];
-        const int cy = gy + M / 2, cx = gx + M / 2;
-        ok = cy >= T.ty0 && cy < T.ty1 && cx >= T.tx0 && cx < T.tx1;
-        if (ok) {
-          ok = gy >= T.ey0 && gx >= T.ex0 && gy + M <= T.ey0 + T.eh && gx + M <= T.ex0 + T.ew;
-          flag = 2u;
-        }
-        if (ok) {
-          jb.grad = T.grad + static_cast<long long>(gy - T.ey0) * T.gld + (gx - T.ex0);
-          jb.gld = T.gld;
-          jb.gslice = T.gslice;
-          if (T.obj != nullptr) {  // the tile's own object, laid out as its gradient
-            jb.win = T.obj + (jb.grad - T.grad);
-            jb.ld = T.gld;
-            jb.sstride = T.gslice;
+        if constexpr (LIST) {
+          ok = a.tiles == nullptr ? take_tile<M>(chunk.t[tk], gy, gx, jb, flag)
+                                  : take_tile<M>(a.tiles[tk], gy, gx, jb, flag);
+        } else {
+          const TileDesc& T = a.tiles[tk];
+          const int cy = gy + M / 2, cx = gx + M / 2;
+          ok = cy >= T.ty0 && cy < T.ty1 && cx >= T.tx0 && cx < T.tx1;
+          if (ok) {
+            ok = gy >= T.ey0 && gx >= T.ex0 && gy + M <= T.ey0 + T.eh && gx + M <= T.ex0 + T.ew;
+            flag = 2u;
+          }
+          if (ok) {
+            jb.grad = T.grad + static_cast<long long>(gy - T.ey0) * T.gld + (gx - T.ex0);
+            jb.gld = T.gld;
+            jb.gslice = T.gslice;
           }
         }
       }
@@ -1126,27 +1152,34 @@ __global__ void __launch_bounds__(64 * kReduceWaves) probe_reduce_kernel(const f
 // other products than in the other gradient launches (losses 2e-11 to 4e-10 apart).
 static bool sums_runs(const KernelArgs& a, int mode) { return a.M == 64 && a.S == 1 && mode == kModeLossGrad; }
 
-template <int M, int MODE, bool SUM = false, bool LIST = false>
+template <int M, int MODE, bool SUM = false>
 static hipError_t launch_fused_t(const KernelArgs& a, int grid, hipStream_t st) {
-  hipLaunchKernelGGL((fused_kernel<M, MODE, SUM, LIST>), dim3(grid), dim3(Geo<M>::T), 0, st, a);
+  hipLaunchKernelGGL((fused_kernel<M, MODE, SUM>), dim3(grid), dim3(Geo<M>::T), 0, st, a, NoTiles{});
+  return hipGetLastError();
+}
+template <int M, bool SUM>
+static hipError_t launch_list_t(const KernelArgs& a, const TileChunk& chunk, int grid, hipStream_t st) {
+  hipLaunchKernelGGL((fused_kernel<M, kModeLossGrad, SUM, true>), dim3(grid), dim3(Geo<M>::T), 0, st, a, chunk);
   return hipGetLastError();
 }
 
 template <int M>
-static hipError_t launch_fused_m(const KernelArgs& a, int mode, int grid, hipStream_t st) {
-  if (a.index != nullptr && mode != kModeLossGrad) return hipErrorInvalidValue;
+static hipError_t launch_fused_m(const KernelArgs& a, int mode, int grid, hipStream_t st, const TileChunk* chunk) {
+  if (a.index != nullptr) {
+    if (mode != kModeLossGrad || chunk == nullptr) return hipErrorInvalidValue;
+    if constexpr (M == 64) {
+      if (sums_runs(a, mode)) return launch_list_t<M, true>(a, *chunk, grid, st);
+    }
+    return launch_list_t<M, false>(a, *chunk, grid, st);
+  }
   switch (mode) {
     case kModeIntensity: return launch_fused_t<M, kModeIntensity>(a, grid, st);
     case kModeLoss: return launch_fused_t<M, kModeLoss>(a, grid, st);
     case kModeLossGrad:
       if constexpr (M == 64) {
-        if (sums_runs(a, mode)) {
-          return a.index != nullptr ? launch_fused_t<M, kModeLossGrad, true, true>(a, grid, st)
-                                    : launch_fused_t<M, kModeLossGrad, true>(a, grid, st);
-        }
+        if (sums_runs(a, mode)) return launch_fused_t<M, kModeLossGrad, true>(a, grid, st);
       }
-      return a.index != nullptr ? launch_fused_t<M, kModeLossGrad, false, true>(a, grid, st)
-                                : launch_fused_t<M, kModeLossGrad>(a, grid, st);
+      return launch_fused_t<M, kModeLossGrad>(a, grid, st);
     case kModeLossGradProbe: return launch_fused_t<M, kModeLossGradProbe>(a, grid, st);
     default: return hipErrorInvalidValue;
   }
@@ -1226,11 +1259,12 @@ static int launch_run(const KernelArgs& a, int mode, long long tile_bytes) {
   return tile_bytes > 0 && object + tile_bytes > (1LL << 30) ? 2 : 8;
 }
 
-hipError_t launch_fused(const KernelArgs& args, int mode, int grid, hipStream_t st, long long tile_bytes) {
+hipError_t launch_fused(const KernelArgs& args, int mode, int grid, hipStream_t st, long long tile_bytes,
+                        const TileChunk* chunk) {
   KernelArgs a = args;
   a.run = launch_run(a, mode, tile_bytes);
-  if (a.M == 128) return launch_fused_m<128>(a, mode, grid, st);
-  if (a.M == 64) return launch_fused_m<64>(a, mode, grid, st);
+  if (a.M == 128) return launch_fused_m<128>(a, mode, grid, st, chunk);
+  if (a.M == 64) return launch_fused_m<64>(a, mode, grid, st, chunk);
   return hipErrorInvalidValue;
 }
 

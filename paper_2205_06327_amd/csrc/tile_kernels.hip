@@ -77,7 +77,7 @@ __device__ __forceinline__ int wave_min(int v) {
   return v;
 }
 
-// One batch of Alg. 1 for every tile (blockIdx.y = tile, blockIdx.z = slice): AccBuf += g,
+// One batch of Alg. 1 for every tile of a chunk (blockIdx.y, blockIdx.z = slice): AccBuf += g,
 // V -= step * g and g = 0, on the bounding box of the windows that the tile's
 // batch touched; g is zero elsewhere, so the rest would not change.  Bound: six
 // accesses per value of that box; the whole extended boxes in separate passes
@@ -86,7 +86,7 @@ __device__ __forceinline__ int wave_min(int v) {
 // first workgroup of a tile also sums its losses, in a fixed order.  The lists are device data: an entry
 // that the gradient launch skips (no such position, listed under another tile than its own, outside the
 // box) takes no part here, and a segment is cut to the batch.
-__global__ void __launch_bounds__(64 * kWaves) tile_step_kernel(const TileDesc* __restrict__ tiles, int M,
+__global__ void __launch_bounds__(64 * kWaves) tile_step_kernel(TileChunk tiles, int tile0, int M,
                                                                const int* __restrict__ pos,
                                                                const int* __restrict__ tile_of_pos, int total,
                                                                const int* __restrict__ index, int n,
@@ -95,8 +95,8 @@ __global__ void __launch_bounds__(64 * kWaves) tile_step_kernel(const TileDesc* 
                                                                double* __restrict__ losses) {
   __shared__ int box[4][kWaves];
   __shared__ double part[64 * kWaves];
-  const int k = static_cast<int>(blockIdx.y), s = static_cast<int>(blockIdx.z);
-  const TileDesc T = tiles[k];
+  const int k = tile0 + static_cast<int>(blockIdx.y), s = static_cast<int>(blockIdx.z);
+  const TileDesc T = tiles.t[blockIdx.y];
   const int lo = max(seg[k], 0), hi = min(seg[k + 1], n);
   const int tid = static_cast<int>(threadIdx.x), lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -168,11 +168,11 @@ __global__ void __launch_bounds__(64 * kWaves) tile_step_kernel(const TileDesc* 
   }
 }
 
-// The accumulated update of Alg. 1 for every tile (blockIdx.y = tile, blockIdx.z = slice):
+// The accumulated update of Alg. 1 for every tile of a chunk (blockIdx.y, blockIdx.z = slice):
 // V -= step * AccBuf, AccBuf = 0.  Bound: four accesses per value.
-__global__ void __launch_bounds__(64 * kWaves) tile_flush_kernel(const TileDesc* __restrict__ tiles, float step) {
-  const int k = static_cast<int>(blockIdx.y), s = static_cast<int>(blockIdx.z);
-  const TileDesc T = tiles[k];
+__global__ void __launch_bounds__(64 * kWaves) tile_flush_kernel(TileChunk tiles, float step) {
+  const int s = static_cast<int>(blockIdx.z);
+  const TileDesc T = tiles.t[blockIdx.y];
   const long long n = static_cast<long long>(T.eh) * T.ew;  // dense
   float2* __restrict__ v = T.obj + s * T.gslice;
   float2* __restrict__ a = T.acc + s * T.gslice;
@@ -194,31 +194,43 @@ hipError_t launch_box_list(const BoxList& list, int S, int rows, hipStream_t st)
   return hipGetLastError();
 }
 
-hipError_t launch_set_tiles(const TileDesc* host, int ntiles, TileDesc* dev, hipStream_t st) {
+namespace {
+// Launches over the tiles, as many at a time as a chunk holds: f(chunk, first tile, tiles).
+template <class F>
+hipError_t for_chunks(const TileDesc* tiles, int ntiles, F&& f) {
   for (int k = 0; k < ntiles; k += TileChunk::kTiles) {
     const int n = ntiles - k < TileChunk::kTiles ? ntiles - k : TileChunk::kTiles;
     TileChunk c;
-    for (int i = 0; i < n; ++i) c.t[i] = host[k + i];
-    hipLaunchKernelGGL(set_tiles_kernel, dim3(1), dim3(256), 0, st, c, n, dev + k);
+    for (int i = 0; i < n; ++i) c.t[i] = tiles[k + i];
+    f(c, k, n);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
+}  // namespace
+
+hipError_t launch_set_tiles(const TileDesc* tiles, int ntiles, TileDesc* dev, hipStream_t st) {
+  return for_chunks(tiles, ntiles, [&](const TileChunk& c, int k, int n) {
+    hipLaunchKernelGGL(set_tiles_kernel, dim3(1), dim3(256), 0, st, c, n, dev + k);
+  });
+}
 
 hipError_t launch_tile_step(const TileDesc* tiles, int ntiles, int S, int M, const int* pos, const int* tile_of_pos,
                             int total, const int* index, int n, const int* seg, float step, const double* loss_work,
                             double* losses, hipStream_t st) {
-  hipLaunchKernelGGL(tile_step_kernel, dim3(32, static_cast<unsigned>(ntiles), static_cast<unsigned>(S)),
-                     dim3(64 * kWaves), 0, st, tiles, M, pos, tile_of_pos, total, index, n, seg, step, loss_work,
-                     losses);
-  return hipGetLastError();
+  return for_chunks(tiles, ntiles, [&](const TileChunk& c, int k, int m) {
+    hipLaunchKernelGGL(tile_step_kernel, dim3(32, static_cast<unsigned>(m), static_cast<unsigned>(S)),
+                       dim3(64 * kWaves), 0, st, c, k, M, pos, tile_of_pos, total, index, n, seg, step, loss_work,
+                       losses);
+  });
 }
 
 hipError_t launch_tile_flush(const TileDesc* tiles, int ntiles, int S, float step, hipStream_t st) {
-  hipLaunchKernelGGL(tile_flush_kernel, dim3(64, static_cast<unsigned>(ntiles), static_cast<unsigned>(S)),
-                     dim3(64 * kWaves), 0, st, tiles, step);
-  return hipGetLastError();
+  return for_chunks(tiles, ntiles, [&](const TileChunk& c, int, int m) {
+    hipLaunchKernelGGL(tile_flush_kernel, dim3(64, static_cast<unsigned>(m), static_cast<unsigned>(S)),
+                       dim3(64 * kWaves), 0, st, c, step);
+  });
 }
 
 }  // namespace ptycho
