@@ -339,11 +339,16 @@ def _dense(ctx: B.Context, plan: TileWalk, bufs) -> bool:
                for p, b in zip(plan.plans, bufs))
 
 
-def _disjoint(*bufs) -> bool:
-    """Whether no two of the dense buffers share memory, which the whole-grid calls that write tile buffers
-    ask for; box by box only the two buffers of an exchange must not."""
-    spans = sorted((b.data_ptr(), b.data_ptr() + b.numel() * b.element_size()) for b in bufs)
-    return all(a[1] <= b[0] for a, b in zip(spans, spans[1:]))
+def _whole_grid(call) -> bool:
+    """Runs a whole-grid call; False where it refuses its buffers, having enqueued nothing: they must not share
+    memory, while box by box only the two buffers of an exchange must not."""
+    try:
+        call()
+    except B.PtychoError as e:
+        if e.name != "PTYCHO_E_ARG":
+            raise
+        return False
+    return True
 
 
 def _tiles(plan: TileWalk, bufs):
@@ -356,8 +361,7 @@ def directional_passes(ctx: B.Context, plan: TileWalk, bufs) -> None:
     every tile row add, back along every row replace.  Dense buffers in memory of their own take one
     launch per step of a pass."""
     ty_n, tx_n = plan.tiles
-    if _dense(ctx, plan, bufs) and _disjoint(*bufs):
-        B.ptycho_tiles_passes(ctx, _tiles(plan, bufs), plan.tiles)
+    if _dense(ctx, plan, bufs) and _whole_grid(lambda: B.ptycho_tiles_passes(ctx, _tiles(plan, bufs), plan.tiles)):
         return
 
     def exchange(src: int, dst: int, replace: bool) -> None:
@@ -385,8 +389,8 @@ def neighbour_add(ctx: B.Context, plan: TileWalk, src, dst) -> None:
     not overlap (tile >= 2 halo); the directional passes cover the general case.  Dense buffers in
     memory of their own take one call that writes every destination once."""
     ty_n, tx_n = plan.tiles
-    if _dense(ctx, plan, src) and _dense(ctx, plan, dst) and _disjoint(*src, *dst):
-        B.ptycho_tiles_neighbour_add(ctx, _tiles(plan, src), dst, plan.tiles)
+    if _dense(ctx, plan, src) and _dense(ctx, plan, dst) and _whole_grid(
+            lambda: B.ptycho_tiles_neighbour_add(ctx, _tiles(plan, src), dst, plan.tiles)):
         return
     for k, p in enumerate(plan.plans):
         ty, tx = divmod(k, tx_n)
